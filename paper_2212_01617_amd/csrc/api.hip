@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/frelbm.h"
@@ -385,6 +386,161 @@ fre_status observe(fre_lattice *L) {
   return FRE_OK;
 }
 
+// M of the current state, without the coupling fields.
+fre_status moments_now(fre_lattice *L) {
+  if (L->a.ternary) launch_moments3(L->a, (int)(L->t & 1));
+  else if (!uses_by_product(L->a)) launch_moments(L->a, (int)(L->t & 1));  // else M is valid
+  HIP_TRY(hipGetLastError());
+  return FRE_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Field reads.  A kernel writes the doubles the caller asked for, in the
+// caller's layout, straight into mapped host memory, a piece of kPackPiece at
+// a time; host threads copy finished pieces on to the caller's (pageable)
+// array.  Writing that array -- first touch of its pages and the copy -- is
+// what bounds a large read: one thread reaches 5 to 8 GB/s, the link 56 GB/s,
+// so up to kPackThreads pieces are under way at once, each thread with a
+// piece of its own.  A read of one piece starts no thread.
+// ---------------------------------------------------------------------------
+constexpr long long kPackPiece = 1 << 18;  // doubles (2 MiB)
+constexpr int kPackThreads = 8;
+
+// One read's mapped buffers.  They are kept for the next read of any lattice
+// (allocating pinned memory costs milliseconds), at most kPinKeep bytes over
+// all threads, and freed when the last lattice is destroyed.
+struct PinBuf {
+  double *p = nullptr;  // host address
+  double *d = nullptr;  // the same memory for kernels
+  size_t bytes = 0;
+};
+constexpr size_t kPinKeep = 64u << 20;
+std::mutex g_pin_mu;
+std::vector<PinBuf> g_pin_free;
+size_t g_pin_kept = 0;
+int g_lattices = 0;
+
+hipError_t pin_take(size_t bytes, PinBuf *out) {
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    for (size_t k = 0; k < g_pin_free.size(); ++k)
+      if (g_pin_free[k].bytes >= bytes) {
+        *out = g_pin_free[k];
+        g_pin_kept -= out->bytes;
+        g_pin_free[k] = g_pin_free.back();
+        g_pin_free.pop_back();
+        return hipSuccess;
+      }
+  }
+  out->bytes = bytes;
+  hipError_t e = hipHostMalloc((void **)&out->p, bytes, hipHostMallocPortable | hipHostMallocMapped);
+  if (e != hipSuccess) return e;
+  e = hipHostGetDevicePointer((void **)&out->d, out->p, 0);
+  if (e != hipSuccess) (void)hipHostFree(out->p);
+  return e;
+}
+
+void pin_give(PinBuf b) {
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    if (g_lattices > 0 && g_pin_kept + b.bytes <= kPinKeep && g_pin_free.size() < g_pin_free.capacity()) {
+      g_pin_free.push_back(b);
+      g_pin_kept += b.bytes;
+      return;
+    }
+  }
+  (void)hipHostFree(b.p);
+}
+
+// Bytes a read of `total` doubles takes: the pieces that are under way at
+// once, in three sizes so that lattices of different sizes share buffers.
+size_t pin_bytes(long long total) {
+  if (total <= kPackPiece / 16) return (size_t)(kPackPiece / 16) * 8;
+  return (size_t)kPackPiece * 8 * (total <= kPackPiece ? 1 : kPackThreads);
+}
+
+// A lattice of n cells exists: its reads find a buffer (one allocated here if
+// none is kept; without it, a read allocates).
+void lattice_counted(long long n) {
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    ++g_lattices;
+    g_pin_free.reserve(32);  // so that pin_give never allocates
+  }
+  PinBuf b;
+  if (pin_take(pin_bytes(8 * n), &b) == hipSuccess) pin_give(b);
+  else (void)hipGetLastError();
+}
+
+void lattice_gone() {
+  std::vector<PinBuf> drop;
+  {
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    if (--g_lattices > 0) return;
+    drop.swap(g_pin_free);
+    g_pin_kept = 0;
+  }
+  for (const PinBuf &b : drop) (void)hipHostFree(b.p);
+}
+
+// nc components (`codes`) of N doubles each into `out`; M (and what else they
+// need) is current on the lattice's stream.  Syncs.
+fre_status read_packed(fre_lattice *L, unsigned long long codes, int nc, double *out) {
+  const long long N = L->n_user, total = (long long)nc * N;
+  PinBuf pin;
+  long long piece = kPackPiece;
+  hipError_t e = pin_take(pin_bytes(total), &pin);
+  if (e != hipSuccess) {  // little pinned memory left: small pieces, one at a time
+    (void)hipGetLastError();
+    piece = kPackPiece / 16;
+    e = pin_take((size_t)piece * 8, &pin);
+    if (e != hipSuccess) return fail(FRE_EDEVICE, "no pinned memory for a read: %s", hipGetErrorString(e));
+  }
+  const int pieces = (int)((total + piece - 1) / piece);
+  const int nw = (int)std::min<long long>({(long long)pieces, (long long)kPackThreads,
+                                           std::max(1LL, (long long)(pin.bytes / 8) / piece)});
+  hipError_t err[kPackThreads];
+  // worker w: pieces w, w + nw, ... through its own part of the buffer
+  auto work = [&](int w, int step) {
+    err[w] = hipSetDevice(L->dev);
+    const size_t at = (size_t)w * (size_t)piece;
+    hipEvent_t ev = nullptr;
+    if (err[w] == hipSuccess) err[w] = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
+    for (int k = w; k < pieces && err[w] == hipSuccess; k += step) {
+      const long long g0 = k * piece;
+      const int n = (int)std::min(piece, total - g0);
+      launch_pack(L->a, L->p.nx, L->p.ny, (int)N, codes, g0, n, pin.d + at);
+      err[w] = hipGetLastError();
+      if (err[w] == hipSuccess) err[w] = hipEventRecord(ev, L->a.stream);
+      if (err[w] == hipSuccess) err[w] = hipEventSynchronize(ev);
+      if (err[w] == hipSuccess) memcpy(out + g0, pin.p + at, (size_t)n * 8);
+    }
+    if (ev) (void)hipEventDestroy(ev);
+  };
+  std::thread th[kPackThreads];
+  bool alone[kPackThreads] = {};
+  for (int w = 1; w < nw; ++w) {
+    err[w] = hipSuccess;
+    try {
+      th[w] = std::thread(work, w, nw);
+    } catch (...) {
+      alone[w] = true;  // no thread to be had: its pieces are done below
+    }
+  }
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  work(0, nw);
+  for (int w = 1; w < nw; ++w) {
+    if (alone[w]) work(w, nw);
+    else th[w].join();
+  }
+  if (cur != L->dev) (void)hipSetDevice(cur);
+  pin_give(pin);
+  for (int w = 0; w < nw; ++w)
+    if (err[w] != hipSuccess) return fail(FRE_EDEVICE, "field read failed: %s", hipGetErrorString(err[w]));
+  return FRE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -485,6 +641,7 @@ fre_status lattice_init(const fre_params *p, void *device_buf, size_t bytes, voi
   INIT_TRY(hipGetLastError());
   INIT_TRY(hipStreamSynchronize(st));
 #undef INIT_TRY
+  lattice_counted(N);
   *out = L;
   return FRE_OK;
 }
@@ -648,61 +805,19 @@ fre_status fre_read_moments(fre_lattice *L, uint32_t field_mask, double *host_ou
   for (int b = 0; b < nfield; ++b)
     if (field_mask & (1u << b)) need += (b == 2 ? 3 : 1) * (size_t)N;
   if (n_doubles < need) return fail(FRE_EINVAL, "output holds %zu doubles, need %zu", n_doubles, need);
-  const Plan &P = L->plan;
-  fre_status s = observe(L);
-  if (s != FRE_OK) return s;
-  std::vector<float> Cv((size_t)P.ncell * 4), AUX((size_t)P.ncell * 4), CM(t3 ? (size_t)P.ncell * 2 : 0);
-  std::vector<uint8_t> mask((size_t)P.ncell);
-  hipStream_t st = L->a.stream;
-  HIP_TRY(hipMemcpyAsync(Cv.data(), L->a.C, Cv.size() * 4, hipMemcpyDeviceToHost, st));
-  if (t3) HIP_TRY(hipMemcpyAsync(CM.data(), L->a.CM, CM.size() * 4, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(AUX.data(), L->a.AUX, AUX.size() * 4, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(mask.data(), L->a.mask, mask.size(), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  const fre_params &p = L->p;
-  double *o = host_out;
+  // components in field-bit order; the moments alone need no coupling pass
+  unsigned long long codes = 0;
+  int nc = 0;
+  bool moments_only = true;
   for (int b = 0; b < nfield; ++b) {
     if (!(field_mask & (1u << b))) continue;
-    int ncomp = b == 2 ? 3 : 1;
-    for (int k = 0; k < ncomp; ++k) {
-      for (int z = 0; z < p.nz; ++z)
-        for (int y = 0; y < p.ny; ++y)
-          for (int x = 0; x < p.nx; ++x) {
-            long long u = x + (long long)p.nx * (y + (long long)p.ny * z);
-            long long e = ext_index(P, x, y, z);
-            double v = 0.0;
-            if (mask[e] == CELL_FLUID && t3) {
-              // C = (rho - 1, phi, psi, Pi), CM = (mu_phi, mu_psi):
-              // mu_rho = (Pi - phi mu_phi - psi mu_psi) / rho
-              const double rho = 1.0 + (double)Cv[4 * e];
-              switch (b) {
-                case 0: v = rho; break;
-                case 1: v = Cv[4 * e + 1]; break;
-                case 2: v = AUX[4 * e + k]; break;
-                case 3: v = ((double)Cv[4 * e + 3] - (double)Cv[4 * e + 1] * CM[2 * e] -
-                             (double)Cv[4 * e + 2] * CM[2 * e + 1]) / rho; break;
-                case 4: v = CM[2 * e]; break;
-                case 5: v = AUX[4 * e + 3]; break;
-                case 6: v = Cv[4 * e + 2]; break;
-                default: v = CM[2 * e + 1]; break;
-              }
-            } else if (mask[e] == CELL_FLUID) {
-              switch (b) {
-                case 0: v = 1.0 + (double)Cv[4 * e]; break;
-                case 1: v = Cv[4 * e + 1]; break;
-                case 2: v = AUX[4 * e + k]; break;
-                // C = (rho - 1, phi, Pi, mu_phi): mu_rho = (Pi - phi mu_phi) / rho
-                case 3: v = ((double)Cv[4 * e + 2] - (double)Cv[4 * e + 1] * Cv[4 * e + 3]) / (1.0 + Cv[4 * e]); break;
-                case 4: v = Cv[4 * e + 3]; break;
-                default: v = AUX[4 * e + 3]; break;
-              }
-            }
-            o[u] = v;
-          }
-      o += N;
-    }
+    static const int first[8] = {PACK_RHO, PACK_PHI, PACK_UX, PACK_MU_RHO, PACK_MU_PHI, PACK_P, PACK_PSI, PACK_MU_PSI};
+    for (int k = 0; k < (b == 2 ? 3 : 1); ++k) codes |= (unsigned long long)(first[b] + k) << (4 * nc++);
+    if (b != 0 && b != 1 && b != 6) moments_only = false;
   }
-  return FRE_OK;
+  fre_status s = moments_only ? moments_now(L) : observe(L);
+  if (s != FRE_OK) return s;
+  return read_packed(L, codes, nc, host_out);
 }
 
 fre_status fre_read_populations(fre_lattice *L, double *f_out, double *g_out, size_t n_doubles_each) {
@@ -1096,6 +1211,7 @@ void fre_lattice_destroy(fre_lattice *L) {
   }
   reset_graph(L);
   delete L;
+  lattice_gone();
 }
 
 // ---------------------------------------------------------------------------

@@ -166,9 +166,19 @@ void launch_init(const LaunchArgs &a);
 void launch_consistent_init(const LaunchArgs &a, long long n);
 // Populations of the storage cells [c0, c0 + n) as [2q + 1][n] floats.
 void launch_read_pops(const LaunchArgs &a, int odd, float *out, long long c0, int n);
-// Ternary lattices: one step, the observables (into AUX; C, CM current), the
+// Fields in the host's layout: n doubles from element g0 of the components
+// `codes` (4 bits each), N cells per component, into `out`.  The moments need
+// M only, the others the state after launch_observe.
+enum PackCode : int {
+  PACK_RHO = 0, PACK_PHI = 1, PACK_UX = 2, PACK_UY = 3, PACK_UZ = 4, PACK_MU_RHO = 5, PACK_MU_PHI = 6, PACK_P = 7,
+  PACK_PSI = 8, PACK_MU_PSI = 9
+};
+void launch_pack(const LaunchArgs &a, int nx, int ny, int N, unsigned long long codes, long long g0, int n,
+                 double *out);
+// Ternary lattices: the moments alone (M), one step, the observables (into AUX; C, CM current), the
 // equilibrium initialisation (M filled from host fields, AUX = u0) and the
 // populations of storage cells [c0, c0 + n) as [3q + 2][n] floats.
+void launch_moments3(const LaunchArgs &a, int odd);
 void launch_step3(const LaunchArgs &a, int odd);
 void launch_observe3(const LaunchArgs &a, int odd);
 void launch_init3(const LaunchArgs &a);

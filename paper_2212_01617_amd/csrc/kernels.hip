@@ -1106,6 +1106,57 @@ __global__ __launch_bounds__(256) void k_read_pops(Pops<Q, S> P, const uint32_t 
   out[(long long)2 * Q * n + t] = lo;
 }
 
+// Fields as the host reads them: `n` doubles from element g0 of the list of
+// components `codes` (4 bits each, in the caller's order), every component
+// the N cells of the fluid domain, x fastest; solid cells read 0.  M (and C,
+// CM, AUX for what is not a moment) must be current.  The consumer is host
+// memory, which the caller maps: the link (56 GB/s) bounds it, so one thread
+// per double, writing 512 contiguous bytes per wave, is enough.  Doing the
+// selection and the widening here sends only what was asked for; copying C
+// and AUX whole and picking them apart on one host thread took 38 ms for rho,
+// phi and u of 256x128x128 cells, this way it is 7 ms (168 MB).
+__global__ __launch_bounds__(256) void k_pack(const LaunchArgs a, int nx, int ny, int N, unsigned long long codes,
+                                              long long g0, int n, double *__restrict__ out) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const long long g = g0 + t;
+  const int k = (int)(g / N), u = (int)(g - (long long)k * N);
+  const int x = u % nx, r = u / nx, y = r % ny, z = r / ny;
+  const Geom &G = a.G;
+  const long long c = (long long)(x + G.off[0]) +
+                      (long long)G.px * ((long long)(y + G.off[1]) + (long long)G.ey * (z + G.off[2]));
+  double v = 0.0;
+  if (a.mask[c] == CELL_FLUID) {
+    const int w = a.ternary ? 4 : 2;  // floats per cell of M
+    const float *m = (const float *)a.M + w * c;
+    const float *aux = (const float *)(a.AUX + c);
+    switch ((int)(codes >> (4 * k)) & 15) {
+      case PACK_RHO: v = 1.0 + (double)m[0]; break;
+      case PACK_PHI: v = m[1]; break;
+      case PACK_PSI: v = m[2]; break;
+      case PACK_UX: v = aux[0]; break;
+      case PACK_UY: v = aux[1]; break;
+      case PACK_UZ: v = aux[2]; break;
+      case PACK_P: v = aux[3]; break;
+      case PACK_MU_PHI: v = a.ternary ? a.CM[c].x : a.C[c].w; break;
+      case PACK_MU_PSI: v = a.CM[c].y; break;
+      default: {  // mu_rho = (Pi - phi mu_phi [- psi mu_psi]) / rho
+        const float4 cc = a.C[c];
+        double num;
+        if (a.ternary) {
+          const float2 mu = a.CM[c];
+          num = __dsub_rn(__dsub_rn((double)cc.w, __dmul_rn((double)cc.y, (double)mu.x)),
+                          __dmul_rn((double)cc.z, (double)mu.y));
+        } else {
+          num = __dsub_rn((double)cc.z, __dmul_rn((double)cc.y, (double)cc.w));
+        }
+        v = num / (1.0 + (double)cc.x);
+      }
+    }
+  }
+  out[t] = v;
+}
+
 // Global sums over fluid cells: compensated FP32 per thread, FP64 across the
 // block; one partial per block (summed on the host in FP64).
 // part[b*8 + k]: k = 0 sum(rho-1), 1 sum phi, 2 sum |phi|, 3..5 sum rho u,
@@ -1685,6 +1736,11 @@ void launch_batch_step(const BatchArgs &b, int cls, int odd) {
   }
 }
 
+void launch_pack(const LaunchArgs &a, int nx, int ny, int N, unsigned long long codes, long long g0, int n,
+                 double *out) {
+  k_pack<<<(n + 255) / 256, 256, 0, a.stream>>>(a, nx, ny, N, codes, g0, n, out);
+}
+
 void launch_reduce(const LaunchArgs &a, double *part) {
   k_reduce<<<reduce_blocks(), 256, 0, a.stream>>>(a.C, a.AUX, a.nbm, a.G.ncell, part);
 }
@@ -1740,6 +1796,18 @@ static void t3_step(const LaunchArgs &a, int odd) {
 void launch_step3(const LaunchArgs &a, int odd) {
   if (a.q == 9) t3_step<9>(a, odd);
   else t3_step<19>(a, odd);
+}
+
+void launch_moments3(const LaunchArgs &a, int odd) {
+  if (a.q == 9) {
+    T3View<9> T = t3_view<9>(a);
+    const dim3 tiles = t3_tiles<9>(a, T);
+    k3_moments<9><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
+  } else {
+    T3View<19> T = t3_view<19>(a);
+    const dim3 tiles = t3_tiles<19>(a, T);
+    k3_moments<19><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
+  }
 }
 
 void launch_observe3(const LaunchArgs &a, int odd) {
