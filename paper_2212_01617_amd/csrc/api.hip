@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -397,14 +398,19 @@ fre_status moments_now(fre_lattice *L) {
 // ---------------------------------------------------------------------------
 // Field reads.  A kernel writes the doubles the caller asked for, in the
 // caller's layout, straight into mapped host memory, a piece of kPackPiece at
-// a time; host threads copy finished pieces on to the caller's (pageable)
-// array.  Writing that array -- first touch of its pages and the copy -- is
-// what bounds a large read: one thread reaches 5 to 8 GB/s, the link 56 GB/s,
-// so up to kPackThreads pieces are under way at once, each thread with a
-// piece of its own.  A read of one piece starts no thread.
+// a time; finished pieces are copied on to the caller's (pageable) array.
+// Writing that array -- first touch of its pages and the copy -- is what
+// bounds a large read: one thread reaches 5 to 8 GB/s, the link 56 GB/s, so
+// kPackThreads threads copy while this one launches and waits.  They sleep
+// between pieces and make no HIP call: threads that each launched and
+// waited for their own pieces spun beside the caller's OpenMP threads and
+// took milliseconds now and then.  Reads of up to kPackAlone pieces start no
+// thread.
 // ---------------------------------------------------------------------------
 constexpr long long kPackPiece = 1 << 18;  // doubles (2 MiB)
-constexpr int kPackThreads = 8;
+constexpr int kPackSlots = 8;              // pieces under way at once
+constexpr int kPackThreads = 7;
+constexpr int kPackAlone = 3;
 
 // One read's mapped buffers.  They are kept for the next read of any lattice
 // (allocating pinned memory costs milliseconds), at most kPinKeep bytes over
@@ -456,7 +462,7 @@ void pin_give(PinBuf b) {
 // once, in three sizes so that lattices of different sizes share buffers.
 size_t pin_bytes(long long total) {
   if (total <= kPackPiece / 16) return (size_t)(kPackPiece / 16) * 8;
-  return (size_t)kPackPiece * 8 * (total <= kPackPiece ? 1 : kPackThreads);
+  return (size_t)kPackPiece * 8 * (total <= kPackPiece ? 1 : kPackSlots);
 }
 
 // A lattice of n cells exists: its reads find a buffer (one allocated here if
@@ -497,47 +503,91 @@ fre_status read_packed(fre_lattice *L, unsigned long long codes, int nc, double 
     if (e != hipSuccess) return fail(FRE_EDEVICE, "no pinned memory for a read: %s", hipGetErrorString(e));
   }
   const int pieces = (int)((total + piece - 1) / piece);
-  const int nw = (int)std::min<long long>({(long long)pieces, (long long)kPackThreads,
-                                           std::max(1LL, (long long)(pin.bytes / 8) / piece)});
-  hipError_t err[kPackThreads];
-  // worker w: pieces w, w + nw, ... through its own part of the buffer
-  auto work = [&](int w, int step) {
-    err[w] = hipSetDevice(L->dev);
-    const size_t at = (size_t)w * (size_t)piece;
-    hipEvent_t ev = nullptr;
-    if (err[w] == hipSuccess) err[w] = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
-    for (int k = w; k < pieces && err[w] == hipSuccess; k += step) {
-      const long long g0 = k * piece;
-      const int n = (int)std::min(piece, total - g0);
-      launch_pack(L->a, L->p.nx, L->p.ny, (int)N, codes, g0, n, pin.d + at);
-      err[w] = hipGetLastError();
-      if (err[w] == hipSuccess) err[w] = hipEventRecord(ev, L->a.stream);
-      if (err[w] == hipSuccess) err[w] = hipEventSynchronize(ev);
-      if (err[w] == hipSuccess) memcpy(out + g0, pin.p + at, (size_t)n * 8);
-    }
-    if (ev) (void)hipEventDestroy(ev);
+  const int slots = (int)std::min<long long>(kPackSlots, std::max(1LL, (long long)(pin.bytes / 8) / piece));
+  hipStream_t st = L->a.stream;
+  auto len = [&](int k) { return (int)std::min(piece, total - k * piece); };
+  auto pack = [&](int k) {
+    launch_pack(L->a, L->p.nx, L->p.ny, (int)N, codes, k * piece, len(k), pin.d + (k % slots) * piece);
+    return hipGetLastError();
   };
-  std::thread th[kPackThreads];
-  bool alone[kPackThreads] = {};
-  for (int w = 1; w < nw; ++w) {
-    err[w] = hipSuccess;
-    try {
-      th[w] = std::thread(work, w, nw);
-    } catch (...) {
-      alone[w] = true;  // no thread to be had: its pieces are done below
+  auto copy = [&](int k) { memcpy(out + k * piece, pin.p + (k % slots) * piece, (size_t)len(k) * 8); };
+  e = hipSuccess;
+  if (pieces <= kPackAlone || slots == 1) {
+    for (int k0 = 0; k0 < pieces && e == hipSuccess; k0 += slots) {
+      const int k1 = std::min(pieces, k0 + slots);
+      for (int k = k0; k < k1 && e == hipSuccess; ++k) e = pack(k);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      for (int k = k0; k < k1 && e == hipSuccess; ++k) copy(k);
     }
+  } else {
+    hipEvent_t ev[kPackSlots] = {};
+    for (int s = 0; s < slots && e == hipSuccess; ++s)
+      e = hipEventCreateWithFlags(&ev[s], hipEventDisableTiming | hipEventReleaseToSystem);
+    std::mutex mu;
+    std::condition_variable work, freed;
+    int ready = 0, next = 0;          // pieces in host memory; pieces taken by a copying thread
+    int holds[kPackSlots];            // the piece a slot holds that is not copied yet, or -1
+    bool stop = false;
+    std::fill(holds, holds + kPackSlots, -1);
+    auto take = [&](std::unique_lock<std::mutex> &lk) {  // copies the next ready piece
+      const int k = next++;
+      lk.unlock();
+      copy(k);
+      lk.lock();
+      holds[k % slots] = -1;
+      freed.notify_one();
+    };
+    auto worker = [&]() {
+      std::unique_lock<std::mutex> lk(mu);
+      for (;;) {
+        work.wait(lk, [&]() { return stop || next < ready; });
+        if (next >= ready) return;
+        take(lk);
+      }
+    };
+    std::thread th[kPackThreads];
+    int nth = 0;
+    try {
+      for (; nth < kPackThreads && nth < pieces - 1; ++nth) th[nth] = std::thread(worker);
+    } catch (...) {
+      // fewer threads, or none: this one copies too
+    }
+    int launched = 0;
+    while (ready < pieces && e == hipSuccess) {
+      {
+        std::unique_lock<std::mutex> lk(mu);
+        while (launched < pieces && holds[launched % slots] < 0 && e == hipSuccess) {
+          holds[launched % slots] = launched;
+          e = pack(launched);
+          if (e == hipSuccess) e = hipEventRecord(ev[launched % slots], st);
+          ++launched;
+        }
+        if (launched == ready && e == hipSuccess) {  // every slot waits to be copied
+          if (next < ready) take(lk);
+          else freed.wait(lk, [&]() { return holds[launched % slots] < 0; });
+          continue;
+        }
+      }
+      if (e == hipSuccess) e = hipEventSynchronize(ev[ready % slots]);
+      if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(mu);
+        ++ready;
+        work.notify_one();
+      }
+    }
+    {
+      std::unique_lock<std::mutex> lk(mu);
+      while (next < ready) take(lk);
+      stop = true;
+      work.notify_all();
+    }
+    for (int w = 0; w < nth; ++w) th[w].join();
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);  // queued pieces still write the buffer
+    for (hipEvent_t v : ev)
+      if (v) (void)hipEventDestroy(v);
   }
-  int cur = 0;
-  (void)hipGetDevice(&cur);
-  work(0, nw);
-  for (int w = 1; w < nw; ++w) {
-    if (alone[w]) work(w, nw);
-    else th[w].join();
-  }
-  if (cur != L->dev) (void)hipSetDevice(cur);
   pin_give(pin);
-  for (int w = 0; w < nw; ++w)
-    if (err[w] != hipSuccess) return fail(FRE_EDEVICE, "field read failed: %s", hipGetErrorString(err[w]));
+  if (e != hipSuccess) return fail(FRE_EDEVICE, "field read failed: %s", hipGetErrorString(e));
   return FRE_OK;
 }
 
