@@ -240,6 +240,7 @@ struct fre_batch {
   std::vector<int> h_range;
   int parity;         // common AA parity of the members
   unsigned classes;   // bit c: class c has members
+  unsigned fills;     // bit c: class c has solid cells to fill
   int rows;           // rows of 64 cells per work item
   int blocks_per_cu;  // persistent grid of the cell kernels
   int ncu;
@@ -330,6 +331,15 @@ fre_status build_mask(fre_lattice *L, const uint8_t *user_mask, std::vector<uint
         nbm[s] = NB_SELF_SOLID | fluid;
         if (fluid) L->fill_host.push_back((int)s);
       }
+  // flat walls closing the last axis and no other solid cell
+  const int last = P.q == 9 ? 1 : 2;
+  L->a.G.flat = 1;
+  for (int a = 0; a < 3; ++a)
+    if (P.per[a] != (a != last)) L->a.G.flat = 0;
+  for (int z = 0; z < p.nz && L->a.G.flat; ++z)
+    for (int y = 0; y < p.ny && L->a.G.flat; ++y)
+      for (int x = 0; x < p.nx; ++x)
+        if (mask[ext_index(P, x, y, z)] != CELL_FLUID) L->a.G.flat = 0;
   // 64-cell row segments whose cells are all fluid with fluid neighbours only
   segf.assign((size_t)(P.ncell / 64), 0);
   for (size_t k = 0; k < segf.size(); ++k) {
@@ -1114,9 +1124,13 @@ fre_status time_kernels(fre_lattice *L, int64_t n, double *kernel_ms) {
   for (auto &e : ev) HIP_TRY(hipEventCreate(&e));
   for (int k = 0; k < nslot; ++k) kernel_ms[k] = -1.0;  // slots this class does not launch
   for (int k = 0; k < K; ++k) kernel_ms[slot[k]] = 0.0;
+  // every stage as a launch of its own: the solid fills too, which the steps
+  // of a lattice between flat walls form inside the other kernels
+  LaunchArgs staged = L->a;
+  staged.G.flat = 0;
   fre_status st = FRE_OK;
   for (int64_t s = 0; s < n; ++s) {
-    launch_step_events(L->a, (int)(L->t & 1), &ev[(size_t)s * (K + 1)]);
+    launch_step_events(staged, (int)(L->t & 1), &ev[(size_t)s * (K + 1)]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { st = fail(FRE_EDEVICE, "launch failed: %s", hipGetErrorString(e)); break; }
     L->t += 1;
@@ -1355,7 +1369,7 @@ fre_status batch_rebuild(fre_batch *B) {
   B->h_cols.clear();
   B->h_fill.clear();
   B->h_range.assign(BATCH_RANGE * N_BATCH_CLASSES, 0);
-  unsigned classes = 0;
+  unsigned classes = 0, fills = 0;
   for (int cls = 0; cls < N_BATCH_CLASSES; ++cls) {
     int *rg = &B->h_range[BATCH_RANGE * cls];
     rg[0] = (int)B->h_work.size();
@@ -1389,12 +1403,14 @@ fre_status batch_rebuild(fre_batch *B) {
           auto &q = cols_of_xcd[ncolrows++ % NXCD_HOST];
           for (int bx = 0; bx < gx; ++bx) q.push_back(make_int4((int)k, bx, by, z));
         }
-      for (int s : L->fill_host) B->h_fill.push_back(make_int2((int)k, s));
+      if (!G.flat)
+        for (int s : L->fill_host) B->h_fill.push_back(make_int2((int)k, s));
     }
     xcd_interleave(rows_of_xcd, B->h_work);
     xcd_interleave(cols_of_xcd, B->h_cols);
     rg[1] = (int)B->h_work.size() - rg[0];
     rg[3] = (int)B->h_fill.size() - rg[2];
+    if (rg[3]) fills |= 1u << cls;
     rg[5] = (int)B->h_cols.size() - rg[4];
   }
   if ((int64_t)B->h_work.size() > B->cap_work || (int64_t)B->h_fill.size() > B->cap_fill)
@@ -1410,8 +1426,10 @@ fre_status batch_rebuild(fre_batch *B) {
     HIP_TRY(hipMemcpyAsync(B->d_fill, B->h_fill.data(), B->h_fill.size() * sizeof(int2), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipMemcpyAsync(B->d_range, B->h_range.data(), BATCH_RANGE * N_BATCH_CLASSES * sizeof(int), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipStreamSynchronize(B->stream));
-  if (classes != B->classes) batch_reset_graph(B);  // the graph launches one sequence per class
+  // the graph launches one sequence per class, with or without fills
+  if (classes != B->classes || fills != B->fills) batch_reset_graph(B);
   B->classes = classes;
+  B->fills = fills;
   return FRE_OK;
 }
 
@@ -1425,6 +1443,7 @@ BatchArgs batch_args(const fre_batch *B) {
   b.range = B->d_range;
   b.grid_cells = B->grid_cells;
   b.grid_fill = B->grid_fill;
+  b.fills = B->fills;
   b.grid_cols = 8 * B->ncu;
   b.rows = B->rows;
   b.stream = B->stream;
@@ -1476,7 +1495,7 @@ fre_status fre_batch_create(void *device_buf, size_t bytes, void *hip_stream, in
   B->d_range = (int *)(B->base + P.o_range);
   B->slot.assign(max_slots, nullptr);
   B->parity = 0;
-  B->classes = 0;
+  B->classes = B->fills = 0;
   B->graph_ok = B->graph_run_ok = false;
   int dev = 0, ncu = 256;
   if (hipGetDevice(&dev) == hipSuccess) {

@@ -23,6 +23,8 @@
 // The coupling fields a fluid cell needs from its neighbours are packed into
 // one float4 per cell, C = (rho - 1, phi, Pi, mu_rho), with mu_phi in a
 // plane of its own; a 32-bit word per cell flags its non-fluid neighbours.
+#include <type_traits>
+
 #include "lbm_device.h"
 #include "kernels.h"
 
@@ -386,6 +388,124 @@ __device__ __forceinline__ void fluid_mean(const float *__restrict__ X, uint32_t
   for (int k = 0; k < NC; ++k) out[k] = num[k] * inv;
 }
 
+// Flat walls (Geom::flat).  A ghost cell's fluid neighbours all lie in the
+// layer of cells next to its wall, so a stencil that reads ghost cells can
+// form their fill -- fluid_mean's sums, in its order -- from values of that
+// layer, which the other threads' cells need too, instead of waiting for a
+// kernel that stores it.  The two fills of a step cost 4.6-5 us each at any
+// size (three dependent loads and a launch).  Without them the 400x200 D2Q9
+// step takes 15.2 instead of 19.4 us, that of 64x32x32 cells 22 instead of 27,
+// and that of 256x128x128 374 instead of 389 (together with the collide's load
+// order).  Masks, rollers
+// and walls on other axes keep the fill kernels: their ghost cells have other
+// neighbours, up to four cells from the reader.
+template <class V> __host__ __device__ constexpr int cn(int i) { return V::D == 3 ? V::cz(i) : V::cy(i); }
+// tangential components of direction i (the second is 0 in 2D)
+template <class V> __host__ __device__ constexpr int ct1(int i) { return V::D == 3 ? V::cy(i) : 0; }
+
+__device__ __forceinline__ int wall_layer(const Geom &G, int D) { return (D == 3 ? G.ez : G.ey) - 2; }
+// whether a cell (on the last axis at n) has ghost neighbours of a flat wall
+template <class V> __device__ __forceinline__ bool by_flat_wall(const Geom &G, int y, int z) {
+  const int n = V::D == 3 ? z : y;
+  return G.flat && (n == 1 || n == wall_layer(G, V::D));
+}
+
+// Fill of the ghost cell of the wall at the low (SIDE = -1) or high (SIDE = 1)
+// end: fetch(dx, dy) is the value of the adjoining layer's cell at that
+// tangential offset from the ghost cell.
+template <int Q, int SIDE, int NC, class Fetch>
+__device__ __forceinline__ void ghost_mean(Fetch fetch, float *out) {
+  using V = VSet<Q>;
+  float num[NC], den = 0.0f;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) num[k] = 0.0f;
+#pragma unroll
+  for (int j = 1; j < Q; ++j) {
+    if (cn<V>(j) != -SIDE) continue;
+    const float w = V::w(j);
+    const float *v = fetch(V::cx(j), ct1<V>(j));
+#pragma unroll
+    for (int k = 0; k < NC; ++k) num[k] += w * v[k];
+    den += w;
+  }
+  const float inv = den > 0.0f ? 1.0f / den : 0.0f;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) out[k] = num[k] * inv;
+}
+
+// (rho - 1, phi) of the ghost cell (x, y, z) of a flat wall from M.
+template <int Q>
+__device__ __forceinline__ float2 ghost_moments(const float2 *__restrict__ M, const Geom &G, int x, int y, int z) {
+  using V = VSet<Q>;
+  const bool low = (V::D == 3 ? z : y) == 0;
+  const int layer = low ? 1 : wall_layer(G, V::D);
+  float2 lay[3][3];
+#pragma unroll
+  for (int b = -1; b <= 1; ++b)
+#pragma unroll
+    for (int a = -1; a <= 1; ++a) {
+      if ((V::D == 2 && b) || (a && b)) continue;
+      const int xs = wrap(x + a, G.ex), ys = V::D == 3 ? wrap(y + b, G.ey) : layer, zs = V::D == 3 ? layer : z;
+      lay[b + 1][a + 1] = M[(long long)xs + (long long)G.px * ((long long)ys + (long long)G.ey * zs)];
+    }
+  auto fetch = [&](int dx, int dy) { return (const float *)&lay[dy + 1][dx + 1]; };
+  float m[2];
+  if (low) ghost_mean<Q, -1, 2>(fetch, m);
+  else ghost_mean<Q, 1, 2>(fetch, m);
+  return make_float2(m[0], m[1]);
+}
+
+// The NC leading floats of a float4 field at the neighbours 1..Q-1 of a cell
+// next to a flat wall, ghost cells filled.  The layer's cells up to two steps
+// away (13 in 3D, 5 in 2D) are loaded first, all at once.
+template <int Q, int NC>
+__device__ __forceinline__ void wall_neighbours(const float4 *__restrict__ X, const Geom &G, const Nbr &N, int x,
+                                                int y, int z, float v[][NC]) {
+  using V = VSet<Q>;
+  constexpr int H1 = V::D == 3 ? 2 : 0;  // reach along the second tangential axis
+  int px[5], py[5];
+  px[2] = x; px[1] = N.ox[0]; px[3] = N.ox[2]; px[0] = wrap(px[1] - 1, G.ex); px[4] = wrap(px[3] + 1, G.ex);
+  py[2] = N.oy[1]; py[1] = N.oy[0]; py[3] = N.oy[2];
+  py[0] = G.px * wrap(wrap(y - 1, G.ey) - 1, G.ey);
+  py[4] = G.px * wrap(wrap(y + 1, G.ey) + 1, G.ey);
+  const int pz = N.oz[1];
+  float lay[5][5][NC];
+#pragma unroll
+  for (int b = 2 - H1; b <= 2 + H1; ++b)
+#pragma unroll
+    for (int a = 0; a < 5; ++a) {
+      if ((a < 2 ? 2 - a : a - 2) + (b < 2 ? 2 - b : b - 2) > 2) continue;
+      const float *q = (const float *)&X[px[a] + py[b] + pz];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) lay[b][a][k] = q[k];
+    }
+#pragma unroll
+  for (int i = 1; i < Q; ++i)
+    if (cn<V>(i) == 0)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) v[i][k] = lay[2 + ct1<V>(i)][2 + V::cx(i)][k];
+  const int n = V::D == 3 ? z : y, top = wall_layer(G, V::D);
+  auto side = [&](auto sgn, bool ghost) {
+    constexpr int SIDE = decltype(sgn)::value;
+    if (ghost) {
+#pragma unroll
+      for (int i = 1; i < Q; ++i)
+        if (cn<V>(i) == SIDE)
+          ghost_mean<Q, SIDE, NC>([&](int dx, int dy) { return lay[2 + ct1<V>(i) + dy][2 + V::cx(i) + dx]; }, v[i]);
+    } else {
+#pragma unroll
+      for (int i = 1; i < Q; ++i)
+        if (cn<V>(i) == SIDE) {
+          const float *q = (const float *)&X[N.template at<V>(i)];
+#pragma unroll
+          for (int k = 0; k < NC; ++k) v[i][k] = q[k];
+        }
+    }
+  };
+  side(std::integral_constant<int, -1>{}, n == 1);
+  side(std::integral_constant<int, 1>{}, n == top);
+}
+
 __device__ __forceinline__ void cell_coords(const Geom &G, int s, int &x, int &y, int &z) {
   x = s % G.px;
   int r = s / G.px;
@@ -444,30 +564,17 @@ __device__ __forceinline__ void store_potential(const LatView<Q, S> &L, long lon
 // mu_rho of a cell from its coupling values C = (rho - 1, phi, Pi, mu_phi).
 __device__ __forceinline__ float coupling_mu_rho(float4 c) { return (c.z - c.y * c.w) / (1.0f + c.x); }
 
-template <int Q, int S>
-__device__ __forceinline__ void stage_potential(const LatView<Q, S> &L, int x, int y, int z) {
-  using V = VSet<Q>;
-  const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  if (L.nbm[c] & NB_SELF_SOLID) return;
-  const Nbr N(L.G, x, y, z);
-  const float2 m0 = L.M[c];
-  float lr, lp;
-  laplacians<Q>([&](int i) { return L.M[N.template at<V>(i)]; }, m0, lr, lp);
-  store_potential<Q, S>(L, c, m0, lr, lp);
-}
-
 // Force of eq. (F) in product-rule form:
 //   -rho grad mu_rho - phi grad mu_phi
 //     = mu_rho grad rho + mu_phi grad phi - grad(rho mu_rho + phi mu_phi),
 // gradients by the lattice stencil (1/cs^2) sum_i w_i c_i X(x + c_i).
-template <int Q>
-__device__ __forceinline__ void force(const float4 *__restrict__ C, const Nbr &N, float mu_rho,
-                                      float mu_phi, float F[3]) {
+template <int Q, class Fetch>
+__device__ __forceinline__ void force_of(Fetch fetch, float mu_rho, float mu_phi, float F[3]) {
   using V = VSet<Q>;
   float gr[3] = {0, 0, 0}, gp[3] = {0, 0, 0}, gq[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 1; i < Q; ++i) {
-    float4 m = C[N.template at<V>(i)];
+    const float3 m = fetch(i);  // (rho - 1, phi, Pi)
     float w = 3.0f * V::w(i);
     if (V::cx(i)) { gr[0] += V::cx(i) * w * m.x; gp[0] += V::cx(i) * w * m.y; gq[0] += V::cx(i) * w * m.z; }
     if (V::cy(i)) { gr[1] += V::cy(i) * w * m.x; gp[1] += V::cy(i) * w * m.y; gq[1] += V::cy(i) * w * m.z; }
@@ -475,6 +582,21 @@ __device__ __forceinline__ void force(const float4 *__restrict__ C, const Nbr &N
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) F[a] = mu_rho * gr[a] + mu_phi * gp[a] - gq[a];
+}
+template <int Q>
+__device__ __forceinline__ void force(const float4 *__restrict__ C, const Geom &G, const Nbr &N, int x, int y, int z,
+                                      float mu_rho, float mu_phi, float F[3]) {
+  using V = VSet<Q>;
+  if (by_flat_wall<V>(G, y, z)) {  // the same for a whole wave
+    float v[Q][3];
+    wall_neighbours<Q, 3>(C, G, N, x, y, z, v);
+    force_of<Q>([&](int i) { return make_float3(v[i][0], v[i][1], v[i][2]); }, mu_rho, mu_phi, F);
+  } else {
+    force_of<Q>([&](int i) {
+      const float4 m = C[N.template at<V>(i)];
+      return make_float3(m.x, m.y, m.z);
+    }, mu_rho, mu_phi, F);
+  }
 }
 
 // f_i^eq - w_i = w_i (rho - 1) + a_i (c_i . m) + w_i q_i (q_i: the
@@ -511,26 +633,35 @@ __device__ __forceinline__ float feq_shifted(float wi, float ai, double drho, fl
 // rounding error of the sum kept (TwoSum, Knuth).
 template <int Q, int S, int ODD, int NT, bool SR = false>
 __device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, long long c,
-                                             const float4 *__restrict__ C,
+                                             const float4 *__restrict__ C, const Geom &G, int x, int y, int z,
                                              const Phys &ph, float (*post)[NT], int tid, float &rho_out,
                                              float &phi_out, float2 &rest_out, uint32_t &rs) {
   using V = VSet<Q>;
   constexpr bool X = S == 0;  // g_0 as hi + lo
-  const float4 cc = C[c];
-  const float mu_phi = cc.w, mu_rho = coupling_mu_rho(cc);
-  float F[3];
-  force<Q>(C, N, mu_rho, mu_phi, F);
   // FP16 storage loads g only after f is collided and stored (fewer live
   // registers); with FP32 storage and the moment sums the split costs
   // registers instead, so f and g are loaded together.
   constexpr bool SPLIT = S == 1;
+  // D2Q9 loads the populations before the force (one round of latency for
+  // both).  D3Q19 loads them after it: with both in flight it holds 166
+  // registers, one after the other 127 to 146 (256x128x128, even parity: FP32
+  // 277 -> 258 us, FP16 159 -> 148; odd parity unchanged).
+  constexpr bool EARLY = Q == 9;
   float df[Q], g[Q];
-  if constexpr (SPLIT) {
+  auto load = [&]() {
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? P.ldfc(i, c) : P.ldfc(opp(i), N.template back<V>(i));
-  } else {
-    load_pops<Q, S, true>(P, N, c, ODD, df, g);
-  }
+      for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? P.ldfc(i, c) : P.ldfc(opp(i), N.template back<V>(i));
+    } else {
+      load_pops<Q, S, true>(P, N, c, ODD, df, g);
+    }
+  };
+  if constexpr (EARLY) load();
+  const float4 cc = C[c];
+  const float mu_phi = cc.w, mu_rho = coupling_mu_rho(cc);
+  float F[3];
+  force<Q>(C, G, N, x, y, z, mu_rho, mu_phi, F);
+  if constexpr (!EARLY) load();
   float drho = 0.0f, j[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -670,7 +801,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
     float rho, phi;
     float2 rest;
     uint32_t rs = SR ? sr_seed(c, L.P.step_key()) : 0u;
-    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, L.C, L.ph, nullptr, 0, rho, phi, rest, rs);
+    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, L.C, L.G, x, y, z, L.ph, nullptr, 0, rho, phi, rest, rs);
     if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
     return;
   }
@@ -686,7 +817,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
       const Nbr N(L.G, x, y, z);
       float rho, phi;
       uint32_t rs = 0u;
-      collide_cell<Q, S, ODD, NT>(L.P, N, c, L.C, L.ph, post, tid, rho, phi, rest, rs);
+      collide_cell<Q, S, ODD, NT>(L.P, N, c, L.C, L.G, x, y, z, L.ph, post, tid, rho, phi, rest, rs);
       if (bits != 0u) bounce_back<Q, S, ODD>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
     }
   }
@@ -768,7 +899,7 @@ __device__ __forceinline__ void stage_pre_collide(const LatView<Q, S> &L, int x,
   const float4 cc = L.C[c];
   const float mu_phi = cc.w, mu_rho = coupling_mu_rho(cc);
   float F[3];
-  force<Q>(L.C, N, mu_rho, mu_phi, F);
+  force<Q>(L.C, L.G, N, x, y, z, mu_rho, mu_phi, F);
   float df[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? L.P.ldf(i, c) : L.P.ldf(opp(i), N.template back<V>(i));
@@ -802,8 +933,7 @@ __device__ __forceinline__ void run_stage(const LatView<Q, S> &L, int x, int y, 
   if constexpr (STAGE == ST_MOMENTS) stage_moments<Q, S, ODD>(L, x, y, z);
   else if constexpr (STAGE == ST_COMBINE) stage_combine<Q, S, ODD>(L, x, y, z);
   else if constexpr (STAGE == ST_PRE_MOMENTS) stage_pre_moments<Q, S, ODD>(L, x, y, z);
-  else if constexpr (STAGE == ST_PRE_COLLIDE) stage_pre_collide<Q, S, ODD>(L, x, y, z);
-  else stage_potential<Q, S>(L, x, y, z);
+  else stage_pre_collide<Q, S, ODD>(L, x, y, z);
 }
 
 // The collide keeps the compiler's register choice (3 waves per SIMD for
@@ -838,7 +968,7 @@ __global__ __launch_bounds__(256) void k_fill(LatView<Q, S> L) {
 // owns a 64 x blockDim.y column of cells over `tz` consecutive planes and
 // keeps three planes of M (with a one-cell halo in x and y) in a ring, so
 // each M value is read from memory about once per block instead of once per
-// neighbour.  Same arithmetic as stage_potential.
+// neighbour.
 constexpr int RING_W = BX + 2;
 using PotRing = float2[3][MAX_ROWS + 2][RING_W];
 
@@ -862,6 +992,8 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
   auto load_plane = [&](int zs, int slot) {
     int zz = zs;
     if (zz < 0 || zz >= G.ez) zz = G.per[2] ? wrap(zz, G.ez) : -1;
+    const int top = wall_layer(G, V::D);
+    const bool ghosts = V::D == 3 && G.flat && (zz == 0 || zz == top + 1);  // a whole plane of them
     for (int k = tid; k < hcells; k += nth) {
       const int hy = k / HW, hx = k - hy * HW;
       float2 v = make_float2(0.0f, 0.0f);
@@ -870,7 +1002,10 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
         bool ok = true;
         if (xg < 0 || xg >= G.ex) { if (G.per[0]) xg = wrap(xg, G.ex); else ok = false; }
         if (yg < 0 || yg >= G.ey) { if (G.per[1]) yg = wrap(yg, G.ey); else ok = false; }
-        if (ok) v = L.M[(long long)xg + (long long)G.px * ((long long)yg + (long long)G.ey * zz)];
+        if (ok) {
+          if (ghosts || (V::D == 2 && G.flat && (yg == 0 || yg == top + 1))) v = ghost_moments<Q>(L.M, G, xg, yg, zz);
+          else v = L.M[(long long)xg + (long long)G.px * ((long long)yg + (long long)G.ey * zz)];
+        }
       }
       ring[slot][hy][hx] = v;
     }
@@ -1064,7 +1199,7 @@ __global__ __launch_bounds__(BX *BY) void k_observe(Pops<Q, S> P, const uint32_t
   }
   const float4 m0 = C[c];
   float F[3];
-  force<Q>(C, N, coupling_mu_rho(m0), m0.w, F);
+  force<Q>(C, G, N, x, y, z, coupling_mu_rho(m0), m0.w, F);
   const float rho = 1.0f + m0.x;
   const float inv = 1.0f / rho;
   // P = cs^2 rho + rho mu_rho + phi mu_phi - psi_b, with Pi = rho mu_rho + phi mu_phi
@@ -1290,17 +1425,28 @@ __global__ __launch_bounds__(256) void k3_fill(T3View<Q> T) {
   }
 }
 
-template <int Q>
-__device__ __forceinline__ void t3_potential_at(const T3View<Q> &T, const Nbr &N, long long c) {
+// INIT: the fill kernel has stored every ghost cell's M
+template <int Q, bool INIT>
+__device__ __forceinline__ void t3_potential_at(const T3View<Q> &T, const Nbr &N, int x, int y, int z, long long c) {
   using V = VSet<Q>;
   const float4 m0 = T.M4[c];
   float ar = 0.0f, ap = 0.0f, aq = 0.0f;
+  auto add = [&](int i, float mx, float my, float mz) {
+    ar += V::w(i) * (mx - m0.x);
+    ap += V::w(i) * (my - m0.y);
+    aq += V::w(i) * (mz - m0.z);
+  };
+  if (!INIT && by_flat_wall<V>(T.G, y, z)) {
+    float v[Q][3];
+    wall_neighbours<Q, 3>(T.M4, T.G, N, x, y, z, v);
 #pragma unroll
-  for (int i = 1; i < Q; ++i) {
-    const float4 m = T.M4[N.template at<V>(i)];
-    ar += V::w(i) * (m.x - m0.x);
-    ap += V::w(i) * (m.y - m0.y);
-    aq += V::w(i) * (m.z - m0.z);
+    for (int i = 1; i < Q; ++i) add(i, v[i][0], v[i][1], v[i][2]);
+  } else {
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      const float4 m = T.M4[N.template at<V>(i)];
+      add(i, m.x, m.y, m.z);
+    }
   }
   float mr, mp, mq;
   chem_pot3(T.ph, m0.x, m0.y, m0.z, 6.0f * ar, 6.0f * ap, 6.0f * aq, mr, mp, mq);
@@ -1314,13 +1460,13 @@ __global__ __launch_bounds__(BX *BY) void k3_potential(T3View<Q> T) {
   long long c;
   if (!cell_of_thread(T.G, x, y, z, c)) return;
   if (T.nbm[c] & NB_SELF_SOLID) return;
-  t3_potential_at<Q>(T, Nbr(T.G, x, y, z), c);
+  t3_potential_at<Q, false>(T, Nbr(T.G, x, y, z), x, y, z, c);
 }
 
 // force and mu_rho of a fluid cell from C4, CM
 template <int Q>
-__device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, long long c, float F[3], float &mu_phi,
-                                         float &mu_psi) {
+__device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, int x, int y, int z, long long c,
+                                         float F[3], float &mu_phi, float &mu_psi) {
   using V = VSet<Q>;
   const float4 cc = T.C4[c];
   const float2 cm = T.CM[c];
@@ -1328,18 +1474,28 @@ __device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, long 
   mu_psi = cm.y;
   const float mu_rho = (cc.w - cc.y * cm.x - cc.z * cm.y) / (1.0f + cc.x);
   float gr[3] = {0, 0, 0}, gp[3] = {0, 0, 0}, gq[3] = {0, 0, 0}, gw[3] = {0, 0, 0};
-#pragma unroll
-  for (int i = 1; i < Q; ++i) {
-    const float4 m = T.C4[N.template at<V>(i)];
+  auto add = [&](int i, float mx, float my, float mz, float mw) {
     const float w = 3.0f * V::w(i);
     const int cv[3] = {V::cx(i), V::cy(i), V::cz(i)};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       if (!cv[a]) continue;
-      gr[a] += cv[a] * w * m.x;
-      gp[a] += cv[a] * w * m.y;
-      gq[a] += cv[a] * w * m.z;
-      gw[a] += cv[a] * w * m.w;
+      gr[a] += cv[a] * w * mx;
+      gp[a] += cv[a] * w * my;
+      gq[a] += cv[a] * w * mz;
+      gw[a] += cv[a] * w * mw;
+    }
+  };
+  if (by_flat_wall<V>(T.G, y, z)) {
+    float v[Q][4];
+    wall_neighbours<Q, 4>(T.C4, T.G, N, x, y, z, v);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) add(i, v[i][0], v[i][1], v[i][2], v[i][3]);
+  } else {
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      const float4 m = T.C4[N.template at<V>(i)];
+      add(i, m.x, m.y, m.z, m.w);
     }
   }
 #pragma unroll
@@ -1390,7 +1546,7 @@ __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   float F[3], mu_phi, mu_psi;
-  t3_force<Q>(T, N, c, F, mu_phi, mu_psi);
+  t3_force<Q>(T, N, x, y, z, c, F, mu_phi, mu_psi);
   // f: BGK with the Guo term, first moments exact as in collide_cell
   float df[Q];
 #pragma unroll
@@ -1452,7 +1608,7 @@ __global__ __launch_bounds__(BX *BY) void k3_init(T3View<Q> T) {
   if (!cell_of_thread(T.G, x, y, z, c)) return;
   if (T.nbm[c] & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
-  t3_potential_at<Q>(T, N, c);
+  t3_potential_at<Q, true>(T, N, x, y, z, c);
   const float4 m0 = T.M4[c];
   const float2 mu = T.CM[c];
   const float4 u4 = T.AUX[c];
@@ -1491,7 +1647,7 @@ __global__ __launch_bounds__(BX *BY) void k3_observe(T3View<Q> T, int odd) {
   }
   const Nbr N(T.G, x, y, z);
   float F[3], mp, mq;
-  t3_force<Q>(T, N, c, F, mp, mq);
+  t3_force<Q>(T, N, x, y, z, c, F, mp, mq);
   float j[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -1575,9 +1731,10 @@ static void cells_launch(const LaunchArgs &a, int odd, int tick = 0) {
   else k_cells<Q, S, STAGE, 0><<<grid, block, 0, a.stream>>>(L);
 }
 
+// the fill of M runs at initialisation for every lattice (k_init reads it)
 template <int Q, int S, int PI>
-static void fill_launch(const LaunchArgs &a) {
-  if (a.n_fill) k_fill<Q, S, PI><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(view_of_args<Q, S>(a));
+static void fill_launch(const LaunchArgs &a, bool init = false) {
+  if (a.n_fill && (init || !a.G.flat)) k_fill<Q, S, PI><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(view_of_args<Q, S>(a));
 }
 
 template <int Q, int S>
@@ -1647,7 +1804,7 @@ static void observe_impl(const LaunchArgs &a, int odd) {
 template <int Q, int S>
 static void init_impl(const LaunchArgs &a) {
   Pops<Q, S> P = make_pops<Q, S>(a);
-  fill_launch<Q, S, 0>(a);
+  fill_launch<Q, S, 0>(a, true);
   k_init<Q, S><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(P, a.nbm, a.M, a.AUX, a.G, a.ph);
   moments_launch<Q, S>(a, 0);  // M of the populations just set
 }
@@ -1716,9 +1873,10 @@ static void batch_step_impl(const BatchArgs &b, int cls, int odd) {
     if (odd) k_batch_cells<Q, S, ST_MOMENTS, 1><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
     else k_batch_cells<Q, S, ST_MOMENTS, 0><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
   }
-  k_batch_fill<Q, S, 0><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
+  const bool fills = (b.fills >> cls) & 1;
+  if (fills) k_batch_fill<Q, S, 0><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
   k_batch_potential<Q, S><<<b.grid_cols, bl, 0, b.stream>>>(b.base, b.inst, b.cols, rp);
-  k_batch_fill<Q, S, 1><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
+  if (fills) k_batch_fill<Q, S, 1><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
   if (odd) k_batch_cells<Q, S, ST_COLLIDE, 1><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
   else k_batch_cells<Q, S, ST_COLLIDE, 0><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
   if (ByProduct<S>::on) {
@@ -1779,9 +1937,10 @@ static void t3_couple(const LaunchArgs &a, int odd) {
   T3View<Q> T = t3_view<Q>(a);
   const dim3 tiles = t3_tiles<Q>(a, T);
   k3_moments<Q><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
-  if (a.n_fill) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
+  const bool fills = a.n_fill && !a.G.flat;
+  if (fills) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
   k3_potential<Q><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(T);
-  if (a.n_fill) k3_fill<Q, 1><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
+  if (fills) k3_fill<Q, 1><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
 }
 
 template <int Q>

@@ -112,6 +112,10 @@ struct Geom {
   int per[3];       // 1 if the axis is periodic
   int off[3];       // ghost offset (1 on wall axes)
   long long ncell;  // px*ey*ez
+  // 1 when the only solid cells are the ghost layers of flat walls closing the
+  // last axis (y in 2D, z in 3D): the stencils then form the values of ghost
+  // cells where they read them, and no fill of solid cells is launched
+  int flat;
 };
 
 struct Phys {
