@@ -331,15 +331,17 @@ fre_status build_mask(fre_lattice *L, const uint8_t *user_mask, std::vector<uint
         nbm[s] = NB_SELF_SOLID | fluid;
         if (fluid) L->fill_host.push_back((int)s);
       }
-  // flat walls closing the last axis and no other solid cell
+  // no solid cell but the ghost layers of flat walls on the last axis, if any
   const int last = P.q == 9 ? 1 : 2;
-  L->a.G.flat = 1;
+  bool plain = true;
   for (int a = 0; a < 3; ++a)
-    if (P.per[a] != (a != last)) L->a.G.flat = 0;
-  for (int z = 0; z < p.nz && L->a.G.flat; ++z)
-    for (int y = 0; y < p.ny && L->a.G.flat; ++y)
+    if (!P.per[a] && a != last) plain = false;
+  for (int z = 0; z < p.nz && plain; ++z)
+    for (int y = 0; y < p.ny && plain; ++y)
       for (int x = 0; x < p.nx; ++x)
-        if (mask[ext_index(P, x, y, z)] != CELL_FLUID) L->a.G.flat = 0;
+        if (mask[ext_index(P, x, y, z)] != CELL_FLUID) plain = false;
+  L->a.G.plain = plain;
+  L->a.G.flat = plain && !P.per[last];
   // 64-cell row segments whose cells are all fluid with fluid neighbours only
   segf.assign((size_t)(P.ncell / 64), 0);
   for (size_t k = 0; k < segf.size(); ++k) {
@@ -1127,7 +1129,7 @@ fre_status time_kernels(fre_lattice *L, int64_t n, double *kernel_ms) {
   // every stage as a launch of its own: the solid fills too, which the steps
   // of a lattice between flat walls form inside the other kernels
   LaunchArgs staged = L->a;
-  staged.G.flat = 0;
+  staged.G.flat = staged.G.plain = 0;
   fre_status st = FRE_OK;
   for (int64_t s = 0; s < n; ++s) {
     launch_step_events(staged, (int)(L->t & 1), &ev[(size_t)s * (K + 1)]);

@@ -609,6 +609,22 @@ __device__ __forceinline__ float feq_shifted(float wi, float ai, double drho, fl
   return (float)__builtin_fma((double)ai, (double)cm, __builtin_fma((double)wi, drho, (double)wq));
 }
 
+// FP16 storage loads g only after f is collided and stored (fewer live
+// registers); with FP32 storage and the moment sums the split costs registers
+// instead, so f and g are loaded together.
+template <int S> constexpr bool split_loads() { return S == 1; }
+// The populations collide_cell starts from: f, and g unless it is split.
+template <int Q, int S, int ODD>
+__device__ __forceinline__ void load_collide(const Pops<Q, S> &P, const Nbr &N, long long c, float *df, float *g) {
+  using V = VSet<Q>;
+  if constexpr (split_loads<S>()) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? P.ldfc(i, c) : P.ldfc(opp(i), N.template back<V>(i));
+  } else {
+    load_pops<Q, S, true>(P, N, c, ODD, df, g);
+  }
+}
+
 // Collision of one fluid cell and streaming of its populations (AA pattern
 // of parity ODD): every population goes to the slot it streams to.  If
 // `post` is given, the stored value of each moving population i > 0 also goes
@@ -631,37 +647,18 @@ __device__ __forceinline__ float feq_shifted(float wi, float ai, double drho, fl
 // alone, tau_g^-1 sum_{i>0} (g_i - g_i^eq), which equals (g_0^eq - g_0) / tau_g
 // since g_0^eq complements the others to phi, and added to hi + lo with the
 // rounding error of the sum kept (TwoSum, Knuth).
-template <int Q, int S, int ODD, int NT, bool SR = false>
-__device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, long long c,
-                                             const float4 *__restrict__ C, const Geom &G, int x, int y, int z,
-                                             const Phys &ph, float (*post)[NT], int tid, float &rho_out,
+//
+// couple(F, mu_phi) forms the force and the cell's mu_phi (and may load the
+// populations after it); df, g: the populations, from load_collide.
+template <int Q, int S, int ODD, int NT, bool SR = false, class Couple>
+__device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, long long c, Couple couple,
+                                             float *df, float *g, const Phys &ph, float (*post)[NT], int tid, float &rho_out,
                                              float &phi_out, float2 &rest_out, uint32_t &rs) {
   using V = VSet<Q>;
   constexpr bool X = S == 0;  // g_0 as hi + lo
-  // FP16 storage loads g only after f is collided and stored (fewer live
-  // registers); with FP32 storage and the moment sums the split costs
-  // registers instead, so f and g are loaded together.
-  constexpr bool SPLIT = S == 1;
-  // D2Q9 loads the populations before the force (one round of latency for
-  // both).  D3Q19 loads them after it: with both in flight it holds 166
-  // registers, one after the other 127 to 146 (256x128x128, even parity: FP32
-  // 277 -> 258 us, FP16 159 -> 148; odd parity unchanged).
-  constexpr bool EARLY = Q == 9;
-  float df[Q], g[Q];
-  auto load = [&]() {
-    if constexpr (SPLIT) {
-#pragma unroll
-      for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? P.ldfc(i, c) : P.ldfc(opp(i), N.template back<V>(i));
-    } else {
-      load_pops<Q, S, true>(P, N, c, ODD, df, g);
-    }
-  };
-  if constexpr (EARLY) load();
-  const float4 cc = C[c];
-  const float mu_phi = cc.w, mu_rho = coupling_mu_rho(cc);
-  float F[3];
-  force<Q>(C, G, N, x, y, z, mu_rho, mu_phi, F);
-  if constexpr (!EARLY) load();
+  constexpr bool SPLIT = split_loads<S>();
+  float F[3], mu_phi;
+  couple(F, mu_phi);
   float drho = 0.0f, j[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -782,47 +779,33 @@ __device__ __forceinline__ void bounce_back(const Pops<Q, S> &P, const Nbr &N, l
   }
 }
 
-// Collide and stream a cell.  With the by-product (FP32), every thread of
-// the 64 x COLLIDE_ROWS block must call this (it holds a barrier); `active`
-// marks threads on a storage cell.  After the barrier each thread forms the
-// first pass of the moment groups of its column: S0 for this plane, UP for
-// the plane above and DN for the plane below (all their sources lie in this
-// plane), from the tile's post-collision values.
-template <int Q, int S, int ODD, bool SR = false>
-__device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int y, int z, bool active) {
+// Force and mu_phi of a cell from the coupling field, and its populations.
+// D2Q9 loads the populations before the force (one round of latency for
+// both).  D3Q19 loads them after it: with both in flight it holds 166
+// registers, one after the other 127 to 146 (256x128x128, even parity: FP32
+// 277 -> 258 us, FP16 159 -> 148; odd parity unchanged).
+template <int Q, int S, int ODD>
+__device__ __forceinline__ auto couple_and_load(const LatView<Q, S> &L, const Nbr &N, int x, int y, int z, long long c,
+                                                float *df, float *g) {
+  constexpr bool EARLY = Q == 9;
+  return [=, &L, &N](float F[3], float &mu_phi) {
+    if constexpr (EARLY) load_collide<Q, S, ODD>(L.P, N, c, df, g);
+    const float4 cc = L.C[c];
+    mu_phi = cc.w;
+    force<Q>(L.C, L.G, N, x, y, z, coupling_mu_rho(cc), mu_phi, F);
+    if constexpr (!EARLY) load_collide<Q, S, ODD>(L.P, N, c, df, g);
+  };
+}
+
+// First pass of the moment groups of the collide's tile (every thread of the
+// 64 x COLLIDE_ROWS block, after the barrier that makes `post` and `live`
+// whole): S0 for this plane, UP for the plane above and DN for the plane below
+// (all their sources lie in this plane).
+template <int Q, int S, int NT>
+__device__ __forceinline__ void moment_sums(const LatView<Q, S> &L, int x, int y, int z, long long c, bool active,
+                                            const float (*post)[NT], const unsigned char *live, int tid,
+                                            float2 rest) {
   using V = VSet<Q>;
-  constexpr int NT = BX * COLLIDE_ROWS;
-  const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  if (!ByProduct<S>::on) {
-    if (!active) return;
-    const uint32_t bits = nb_word<Q, S>(L, c);
-    if (bits & NB_SELF_SOLID) return;
-    const Nbr N(L.G, x, y, z);
-    float rho, phi;
-    float2 rest;
-    uint32_t rs = SR ? sr_seed(c, L.P.step_key()) : 0u;
-    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, L.C, L.G, x, y, z, L.ph, nullptr, 0, rho, phi, rest, rs);
-    if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
-    return;
-  }
-  __shared__ float post[2 * (Q - 1)][NT];
-  __shared__ unsigned char live[NT];
-  const int tid = threadIdx.y * BX + threadIdx.x;
-  bool fluid = false;
-  float2 rest = make_float2(0.0f, 0.0f);
-  if (active) {
-    const uint32_t bits = nb_word<Q, S>(L, c);
-    fluid = !(bits & NB_SELF_SOLID);
-    if (fluid) {
-      const Nbr N(L.G, x, y, z);
-      float rho, phi;
-      uint32_t rs = 0u;
-      collide_cell<Q, S, ODD, NT>(L.P, N, c, L.C, L.G, x, y, z, L.ph, post, tid, rho, phi, rest, rs);
-      if (bits != 0u) bounce_back<Q, S, ODD>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
-    }
-  }
-  live[tid] = fluid ? 1 : 0;
-  __syncthreads();
   // XE entries of this row: lane e < NE stores entry e of side 0 (first
   // column), lane NE + e entry e of side 1 (last column), if that cell is fluid
   if (threadIdx.x < 2 * XEdge<V>::NE) {
@@ -857,6 +840,50 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
     if (zu >= 0) L.PU[c + (zu - z) * pl] = grp[2];
     if (zd >= 0) L.PD[c + (zd - z) * pl] = grp[0];
   }
+}
+
+// Collide and stream a cell.  With the by-product (FP32), every thread of
+// the 64 x COLLIDE_ROWS block must call this (it holds a barrier); `active`
+// marks threads on a storage cell.
+template <int Q, int S, int ODD, bool SR = false>
+__device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int y, int z, bool active) {
+  constexpr int NT = BX * COLLIDE_ROWS;
+  const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
+  if (!ByProduct<S>::on) {
+    if (!active) return;
+    const uint32_t bits = nb_word<Q, S>(L, c);
+    if (bits & NB_SELF_SOLID) return;
+    const Nbr N(L.G, x, y, z);
+    float rho, phi;
+    float2 rest;
+    uint32_t rs = SR ? sr_seed(c, L.P.step_key()) : 0u;
+    float df[Q], g[Q];
+    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, nullptr,
+                                    0, rho, phi, rest, rs);
+    if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
+    return;
+  }
+  __shared__ float post[2 * (Q - 1)][NT];
+  __shared__ unsigned char live[NT];
+  const int tid = threadIdx.y * BX + threadIdx.x;
+  bool fluid = false;
+  float2 rest = make_float2(0.0f, 0.0f);
+  if (active) {
+    const uint32_t bits = nb_word<Q, S>(L, c);
+    fluid = !(bits & NB_SELF_SOLID);
+    if (fluid) {
+      const Nbr N(L.G, x, y, z);
+      float rho, phi;
+      uint32_t rs = 0u;
+      float df[Q], g[Q];
+      collide_cell<Q, S, ODD, NT>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, post,
+                                  tid, rho, phi, rest, rs);
+      if (bits != 0u) bounce_back<Q, S, ODD>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
+    }
+  }
+  live[tid] = fluid ? 1 : 0;
+  __syncthreads();
+  moment_sums<Q, S>(L, x, y, z, c, active, post, live, tid, rest);
 }
 
 // ---------------------------------------------------------------------------
@@ -1041,6 +1068,146 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_potential_zm(LatView<Q, S> L, 
   const uint32_t uch = udiv(ur, L.tm.dgy);
   const int by = (int)(ur - uch * (uint32_t)L.tm.gy), z0 = (int)uch * tz;
   potential_column<Q, S>(L, ring, (int)ubx, by, z0, min(z0 + tz, L.G.ez));
+}
+
+// ---------------------------------------------------------------------------
+// D2Q9: collide with the potential formed on chip, for a lattice without
+// solid cells but flat walls on its last axis (Geom::plain).  A block stages
+// the moments of its 64 x COLLIDE_ROWS tile and two cells around it in LDS,
+// forms Pi there with one cell around the tile, and collides with the force
+// taken from LDS: the potential's launch and the coupling field (written and
+// read back) go.  A 2D step is a chain of short launches, so a launch less is
+// what counts: a step takes 13.0 instead of 15.2 us at 400x200 FP32, 10.2
+// instead of 12.1 at 333x150 FP16 (and 157 instead of 194 at 2048x2048, where
+// it is the bytes).  In 3D the same fusion (a block marching in z, four planes of moments
+// and three of Pi in LDS) lost: 385-411 us instead of 290 for both kernels
+// at 256x128x128 FP32, 210-235 instead of 200 in FP16, since 68 KB of LDS
+// leave two blocks per CU and each plane has three barriers.
+//
+// The arithmetic is that of potential_column and of the collide on the
+// coupling field.  Next to a flat wall the ghost cells' Pi is the mean over
+// three cells of the layer at the wall, so along x Pi is formed two and the
+// moments are staged three cells beyond the tile.
+// ---------------------------------------------------------------------------
+// v wrapped into [0, n) for -3 <= v < n + 3 (a periodic axis of any length)
+__device__ __forceinline__ int wrap_far(int v, int n) {
+  if (n >= 3) return wrap(v, n);
+  v %= n;
+  return v < 0 ? v + n : v;
+}
+
+template <int S, int ODD, bool SR = false>
+__global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L) {
+  constexpr int Q = 9, R = COLLIDE_ROWS, NT = BX * R;
+  using V = VSet<Q>;
+  constexpr bool BP = ByProduct<S>::on;
+  constexpr int HX = 3, HY = 2, PX = 2, PY = 1;  // reach of the moments and of Pi
+  __shared__ float2 mom[R + 2 * HY][BX + 2 * HX];
+  __shared__ float pis[R + 2 * PY][BX + 2 * PX];
+  __shared__ float mus[R][BX];
+  __shared__ float post[BP ? 2 * (Q - 1) : 1][BP ? NT : 1];
+  __shared__ unsigned char live[BP ? NT : 1];
+  const Geom &G = L.G;
+  uint32_t ubx, uby;
+  tile_of_block(L.tm, blockIdx.x, ubx, uby);
+  const int xlo = (int)ubx * BX, ylo = (int)uby * R;
+  const int w = min(BX, G.ex - xlo), h = min(R, G.ey - ylo);
+  const int tx = threadIdx.x, ty = __builtin_amdgcn_readfirstlane((int)threadIdx.y), tid = ty * BX + tx;
+  const int top = wall_layer(G, V::D);
+
+  // the moments first, then the populations (loads return in order): these
+  // arrive while Pi is formed.  The last wave also takes the columns left and
+  // right of the tile.
+  auto moments = [&](int r, int c) {
+    if (r >= h + HY || c >= w + HX) return make_float2(0.0f, 0.0f);
+    int yg = ylo + r;
+    if (G.flat) {
+      if (yg < 0 || yg > top + 1) return make_float2(0.0f, 0.0f);
+    } else {
+      yg = wrap_far(yg, G.ey);
+    }
+    const int xg = wrap_far(xlo + c, G.ex);
+    if (G.flat && (yg == 0 || yg == top + 1)) return ghost_moments<Q>(L.M, G, xg, yg, 0);
+    return L.M[(uint32_t)(G.px * yg) + (uint32_t)xg];
+  };
+  constexpr int NR = (R + 2 * HY) / R;  // rows per wave
+  static_assert(NR * R == R + 2 * HY && (R + 2 * HY) * 2 * HX <= BX && (R + 2 * PY) * 2 * PX <= BX, "tile halo");
+  float2 f[NR + 1];
+#pragma unroll
+  for (int k = 0; k < NR; ++k) f[k] = moments(ty - HY + k * R, tx);
+  const int sr = tx / (2 * HX) - HY, sj = tx % (2 * HX), sc = sj < HX ? sj - HX : BX + sj - HX;
+  const bool side = ty == R - 1 && sr < R + HY;
+  if (side) f[NR] = moments(sr, sc);
+  const int x = xlo + tx, y = ylo + ty;
+  const bool active = tx < w && ty < h;
+  const long long c = (long long)x + (long long)G.px * y;
+  const bool fluid = active && (!G.flat || (y >= 1 && y <= top));
+  const Nbr N(G, x, y, 0);
+  float df[Q], g[Q];
+  if (fluid) load_collide<Q, S, ODD>(L.P, N, c, df, g);
+#pragma unroll
+  for (int k = 0; k < NR; ++k) mom[ty + k * R][tx + HX] = f[k];
+  if (side) mom[sr + HY][sc + HX] = f[NR];
+  __syncthreads();
+
+  auto form_pi = [&](int r, int cc) {
+    if (r >= h + PY || cc >= w + PX) return;
+    if (G.flat && (ylo + r < 1 || ylo + r > top)) return;  // ghost rows: below
+    auto at = [&](int dx, int dy) { return mom[r + HY + dy][cc + HX + dx]; };
+    const float2 m0 = at(0, 0);
+    float lr, lp, mr, mp;
+    laplacians<Q>([&](int i) { return at(V::cx(i), V::cy(i)); }, m0, lr, lp);
+    chem_pot(L.ph, m0.x, m0.y, lr, lp, mr, mp);
+    pis[r + PY][cc + PX] = (1.0f + m0.x) * mr + m0.y * mp;
+    if (r >= 0 && r < R && cc >= 0 && cc < BX) mus[r][cc] = mp;
+  };
+#pragma unroll 1
+  for (int r = ty - PY; r < R + PY; r += R) form_pi(r, tx);
+  const int pr = tx / (2 * PX) - PY, pj = tx % (2 * PX);
+  if (ty == R - 1 && pr < R + PY) form_pi(pr, pj < PX ? pj - PX : BX + pj - PX);
+  if (G.flat) {
+    __syncthreads();
+    // Pi of the ghost rows within reach of the tile, from the layer at the wall
+    auto ghosts = [&](int rg, int rs, auto sgn) {
+      constexpr int SIDE = decltype(sgn)::value;
+      if (rg < -PY || rg >= h + PY) return;
+      auto put = [&](int cc) {
+        if (cc >= w + 1) return;
+        float v;
+        ghost_mean<Q, SIDE, 1>([&](int dx, int) { return &pis[rs + PY][cc + PX + dx]; }, &v);
+        pis[rg + PY][cc + PX] = v;
+      };
+      if (ty == 0) put(tx);
+      if (ty == 1 && tx < 2) put(tx ? BX : -1);
+    };
+    ghosts(0 - ylo, 1 - ylo, std::integral_constant<int, -1>{});
+    ghosts(top + 1 - ylo, top - ylo, std::integral_constant<int, 1>{});
+  }
+  __syncthreads();
+
+  float2 rest = make_float2(0.0f, 0.0f);
+  if (fluid) {
+    float rho, phi;
+    uint32_t rs = SR ? sr_seed(c, L.P.step_key()) : 0u;
+    auto couple = [&](float F[3], float &mu_phi) {
+      const float2 m0 = mom[ty + HY][tx + HX];
+      mu_phi = mus[ty][tx];
+      force_of<Q>([&](int i) {
+        const float2 m = mom[ty + HY + V::cy(i)][tx + HX + V::cx(i)];
+        return make_float3(m.x, m.y, pis[ty + PY + V::cy(i)][tx + PX + V::cx(i)]);
+      }, coupling_mu_rho(make_float4(m0.x, m0.y, pis[ty + PY][tx + PX], mu_phi)), mu_phi, F);
+    };
+    float(*tile)[NT] = nullptr;
+    if constexpr (BP) tile = post;
+    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple, df, g, L.ph, tile, tid, rho, phi, rest, rs);
+    const uint32_t bits = G.flat && (y == 1 || y == top) ? L.nbm[c] : 0u;
+    if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, G, L.ph, x, y, 0, rho, phi, rs);
+  }
+  if constexpr (BP) {
+    live[tid] = fluid ? 1 : 0;
+    __syncthreads();
+    moment_sums<Q, S>(L, x, y, 0, c, active, post, live, tid, rest);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1755,6 +1922,22 @@ static void potential_launch(const LaunchArgs &a) {
   k_potential_zm<Q, S><<<dim3((unsigned)(tiles * nch)), dim3(BX, sh.rows, 1), 0, a.stream>>>(L, tz);
 }
 
+template <int S>
+static void collide_2d_launch(const LaunchArgs &a, int odd) {
+  LatView<9, S> L = view_of_args<9, S>(a);
+  const dim3 grid = tile_grid(a.G, COLLIDE_ROWS), block = cell_block();
+  L.tm = TileMap(a.G.ex, a.G.ey, COLLIDE_ROWS, (int)grid.x, a.shape[SHAPE_COLLIDE].xcd);
+  if constexpr (S == 1) {
+    if (a.ctr) {  // stochastic rounding
+      if (odd) k_collide_2d<S, 1, true><<<grid, block, 0, a.stream>>>(L);
+      else k_collide_2d<S, 0, true><<<grid, block, 0, a.stream>>>(L);
+      return;
+    }
+  }
+  if (odd) k_collide_2d<S, 1><<<grid, block, 0, a.stream>>>(L);
+  else k_collide_2d<S, 0><<<grid, block, 0, a.stream>>>(L);
+}
+
 // Coupling fields of the current state: solid fills of rho, phi, then
 // mu_rho, mu_phi, Pi, then the solid fill of Pi.
 template <int Q, int S>
@@ -1780,8 +1963,14 @@ static void step_seq(const LaunchArgs &a, int odd, hipEvent_t *ev) {
     moments_launch<Q, S>(a, odd, 1);  // the step's moments advance the rounding counter
     if (ev) (void)hipEventRecord(ev[k++], a.stream);
   }
-  couple_seq<Q, S>(a, ev, k);
-  cells_launch<Q, S, ST_COLLIDE>(a, odd);
+  bool fused = false;
+  if constexpr (Q == 9) {
+    if ((fused = a.G.plain)) collide_2d_launch<S>(a, odd);
+  }
+  if (!fused) {
+    couple_seq<Q, S>(a, ev, k);
+    cells_launch<Q, S, ST_COLLIDE>(a, odd);
+  }
   if (ev) (void)hipEventRecord(ev[k++], a.stream);
   if (ByProduct<S>::on) {
     cells_launch<Q, S, ST_COMBINE>(a, odd ^ 1);

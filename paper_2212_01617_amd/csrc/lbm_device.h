@@ -116,6 +116,9 @@ struct Geom {
   // last axis (y in 2D, z in 3D): the stencils then form the values of ghost
   // cells where they read them, and no fill of solid cells is launched
   int flat;
+  // 1 when there is no solid cell but such ghost layers (none at all if every
+  // axis is periodic): the D2Q9 collide then forms the potential itself
+  int plain;
 };
 
 struct Phys {

@@ -1,5 +1,6 @@
 """Lattices between flat walls on the last axis form the values of ghost cells
-inside the stencil kernels; profiled steps store them with the fill kernels, a
+inside the stencil kernels, and D2Q9 lattices without solid cells form the
+potential inside the collide; profiled steps store fills and potential, a
 launch per stage.  Both have to give bitwise the same populations, down to one
 cell per axis (where a neighbour two steps away is the cell itself, and both
 walls fill from one layer), in every storage; ternary lattices are held to the
@@ -23,10 +24,10 @@ def _lib():
     ensure_gpu_lib()
 
 
-def _inputs(kind, shape):
+def _inputs(kind, shape, walls=True):
     nx, ny, nz = shape
     sh, axis = (nz, ny, nx), (1 if kind == 0 else 2)
-    bc = tuple(int(a == axis) for a in range(3))
+    bc = tuple(int(walls and a == axis) for a in range(3))
     wu = np.zeros((3, 2, 3)); wu[axis, 0, 0] = -0.01; wu[axis, 1, 0] = 0.012
     if kind == 1:
         wu[axis, 1, 1] = 0.004
@@ -44,8 +45,18 @@ SHAPES = [(0, (1, 1, 1)), (0, (2, 1, 1)), (0, (3, 2, 1)), (0, (64, 3, 1)), (0, (
 
 @pytest.mark.parametrize("storage,sr", [(0, False), (1, False), (1, True)])
 @pytest.mark.parametrize("kind,shape", SHAPES)
-def test_fills_in_the_stencils_equal_fill_kernels(kind, shape, storage, sr):
-    bc, wu, phi0, rho0, u0 = _inputs(kind, shape)
+def test_fused_steps_equal_staged_steps(kind, shape, storage, sr):
+    _equal(kind, shape, storage, sr, True)
+
+
+@pytest.mark.parametrize("storage,sr", [(0, False), (1, False), (1, True)])
+@pytest.mark.parametrize("kind,shape", [s for s in SHAPES if s[0] == 0])
+def test_fused_steps_equal_staged_steps_periodic(kind, shape, storage, sr):
+    _equal(kind, shape, storage, sr, False)
+
+
+def _equal(kind, shape, storage, sr, walls):
+    bc, wu, phi0, rho0, u0 = _inputs(kind, shape, walls)
     p = F.make_params(kind, shape, storage=storage, bc=bc, wall_u=wu, stochastic_rounding=sr,
                       kappa1=0.16, kappa2=0.12, alpha=1.0, tau_f=0.8, tau_g=1.1, M=0.1)
     a, b = (F.Lattice(p, phi0, rho0, u0, stream=torch.cuda.Stream()) for _ in range(2))
