@@ -292,7 +292,7 @@ void fre_lattice_destroy(fre_lattice *L);
  * class present, one persistent launch per stage of the step over a
  * device-side list of (lattice, block) work items; the list and its length
  * live in device memory, so lattices join and leave without recapturing the
- * batch's HIP graph.  A lattice advanced inside a batch takes exactly the
+ * batch's HIP graphs.  A lattice advanced inside a batch takes exactly the
  * arithmetic it takes alone (bitwise the same populations).
  * ------------------------------------------------------------------------- */
 
@@ -324,6 +324,9 @@ fre_status fre_batch_add(fre_batch *B, fre_lattice *L, int32_t *slot);
 fre_status fre_batch_remove(fre_batch *B, int32_t slot);
 
 /* Advance every member n >= 0 steps, asynchronously on the batch's stream.
+ * Runs of four steps and more replay one graph per class, the classes side by
+ * side on streams of the batch's own (default priority) that wait for what
+ * is queued on the batch's stream and that it waits for in turn.
  * FRE_ESTATE if a member has failed. */
 fre_status fre_batch_step(fre_batch *B, int64_t n);
 

@@ -244,10 +244,13 @@ struct fre_batch {
   int rows;           // rows of 64 cells per work item
   int blocks_per_cu;  // persistent grid of the cell kernels
   int ncu;
-  hipGraphExec_t graph;      // two steps starting at even parity
-  bool graph_ok;
-  hipGraphExec_t graph_run;  // kGraphRun steps starting at even parity
-  bool graph_run_ok;
+  // per class: two steps, and kGraphRun steps, starting at even parity (null
+  // until captured)
+  hipGraphExec_t graph[N_BATCH_CLASSES], graph_run[N_BATCH_CLASSES];
+  // the classes' own streams (null until two classes are stepped together),
+  // and the events that fork them from the batch's stream and join them
+  hipStream_t cls_stream[N_BATCH_CLASSES];
+  hipEvent_t fork, join[N_BATCH_CLASSES];
   int grid_cells, grid_fill;
 };
 
@@ -1337,10 +1340,14 @@ Inst inst_of(const fre_lattice *L, const void *base) {
 
 // As reset_graph: the batch's queued graph launches finish first.
 void batch_reset_graph(fre_batch *B) {
-  if (B->graph_ok || B->graph_run_ok) (void)hipStreamSynchronize(B->stream);
-  if (B->graph_ok) (void)hipGraphExecDestroy(B->graph);
-  if (B->graph_run_ok) (void)hipGraphExecDestroy(B->graph_run);
-  B->graph_ok = B->graph_run_ok = false;
+  bool any = false;
+  for (int c = 0; c < N_BATCH_CLASSES; ++c) any = any || B->graph[c] || B->graph_run[c];
+  if (any) (void)hipStreamSynchronize(B->stream);
+  for (int c = 0; c < N_BATCH_CLASSES; ++c)
+    for (hipGraphExec_t *g : {&B->graph[c], &B->graph_run[c]}) {
+      if (*g) (void)hipGraphExecDestroy(*g);
+      *g = nullptr;
+    }
 }
 
 // Work-list order for the XCDs.  The persistent cell kernels walk a class's
@@ -1458,6 +1465,83 @@ void batch_launch_step(const fre_batch *B, int odd) {
     if (B->classes & (1u << cls)) launch_batch_step(b, cls, odd);
 }
 
+// A graph of `pairs` even + odd step pairs of one class.
+fre_status batch_capture(const fre_batch *B, int cls, int pairs, hipGraphExec_t *out) {
+  if (*out) return FRE_OK;
+  const BatchArgs b = batch_args(B);
+  hipGraph_t g;
+  HIP_TRY(hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
+  for (int k = 0; k < pairs; ++k) {
+    launch_batch_step(b, cls, 0);
+    launch_batch_step(b, cls, 1);
+  }
+  hipError_t e = hipStreamEndCapture(B->stream, &g);
+  if (e != hipSuccess) return fail(FRE_EDEVICE, "batch graph capture failed: %s", hipGetErrorString(e));
+  e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(g);
+  if (e != hipSuccess) {
+    *out = nullptr;
+    return fail(FRE_EDEVICE, "batch graph instantiate failed: %s", hipGetErrorString(e));
+  }
+  return FRE_OK;
+}
+
+// n (even) steps from even parity, by graph replay.  The classes hold
+// different lattices, so each runs its n steps on a stream of its own, forked
+// from the batch's stream and joined to it at the end: the short launches
+// and the last waves of one class run under the others.  (Two classes of 2D
+// and two of 3D lattices, eight members: the step's kernels add up to 350 us,
+// one class after another; side by side it takes about 270.)  The first class
+// present runs on the batch's stream itself.
+fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
+  hipStream_t st = B->stream;
+  int first = -1, others = 0;
+  for (int c = 0; c < N_BATCH_CLASSES; ++c)
+    if (B->classes & (1u << c)) {
+      if (first < 0) first = c;
+      else ++others;
+      // every graph and stream before the first launch
+      if (n >= kGraphRun) {
+        if (fre_status s = batch_capture(B, c, kGraphRun / 2, &B->graph_run[c])) return s;
+      }
+      if (n % kGraphRun) {
+        if (fre_status s = batch_capture(B, c, 1, &B->graph[c])) return s;
+      }
+      if (c != first && !B->cls_stream[c]) {
+        HIP_TRY(hipEventCreateWithFlags(&B->join[c], hipEventDisableTiming));
+        HIP_TRY(hipStreamCreateWithFlags(&B->cls_stream[c], hipStreamNonBlocking));
+      }
+    }
+  if (others) {
+    if (!B->fork) HIP_TRY(hipEventCreateWithFlags(&B->fork, hipEventDisableTiming));
+    HIP_TRY(hipEventRecord(B->fork, st));
+  }
+  hipError_t e = hipSuccess;
+  for (int c = N_BATCH_CLASSES - 1; c >= first && e == hipSuccess; --c) {
+    if (!(B->classes & (1u << c))) continue;
+    hipStream_t cs = c == first ? st : B->cls_stream[c];
+    if (c != first) e = hipStreamWaitEvent(cs, B->fork, 0);
+    for (int64_t k = n; k > 0 && e == hipSuccess;) {
+      const bool run = k >= kGraphRun;
+      e = hipGraphLaunch(run ? B->graph_run[c] : B->graph[c], cs);
+      k -= run ? kGraphRun : 2;
+    }
+    if (c != first && e == hipSuccess) e = hipEventRecord(B->join[c], cs);
+  }
+  for (int c = first + 1; c < N_BATCH_CLASSES && e == hipSuccess; ++c)
+    if (B->classes & (1u << c)) e = hipStreamWaitEvent(st, B->join[c], 0);
+  if (e != hipSuccess) {
+    // the classes are at different steps now: nothing may go on from here
+    for (int c = 0; c < N_BATCH_CLASSES; ++c)
+      if (B->cls_stream[c]) (void)hipStreamSynchronize(B->cls_stream[c]);
+    for (fre_lattice *L : B->slot)
+      if (L) L->state = 1;
+    return fail(FRE_EDEVICE, "batch graph launch failed: %s", hipGetErrorString(e));
+  }
+  *done += n;
+  return FRE_OK;
+}
+
 }  // namespace
 
 fre_status fre_batch_footprint(int32_t max_slots, int64_t max_work, int64_t max_fill, size_t *bytes) {
@@ -1498,7 +1582,6 @@ fre_status fre_batch_create(void *device_buf, size_t bytes, void *hip_stream, in
   B->slot.assign(max_slots, nullptr);
   B->parity = 0;
   B->classes = B->fills = 0;
-  B->graph_ok = B->graph_run_ok = false;
   int dev = 0, ncu = 256;
   if (hipGetDevice(&dev) == hipSuccess) {
     int v = 0;
@@ -1579,35 +1662,10 @@ fre_status fre_batch_step(fre_batch *B, int64_t n) {
     for (int64_t k = 0; k < n && s == FRE_OK; ++k) s = one();
   } else {
     if (B->parity) { s = one(); --n; }
-    // a graph of `pairs` even + odd step pairs
-    auto capture = [&](int pairs, hipGraphExec_t *out) -> fre_status {
-      hipGraph_t g;
-      HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-      for (int k = 0; k < pairs; ++k) {
-        batch_launch_step(B, 0);
-        batch_launch_step(B, 1);
-      }
-      hipError_t e = hipStreamEndCapture(st, &g);
-      if (e != hipSuccess) return fail(FRE_EDEVICE, "batch graph capture failed: %s", hipGetErrorString(e));
-      e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(g);
-      if (e != hipSuccess) return fail(FRE_EDEVICE, "batch graph instantiate failed: %s", hipGetErrorString(e));
-      return FRE_OK;
-    };
-    // runs of kGraphRun steps, then pairs, as for a single lattice
-    auto replay = [&](hipGraphExec_t *gx, bool *ok, int steps) {
-      if (s == FRE_OK && n >= steps && !*ok) {
-        s = capture(steps / 2, gx);
-        *ok = s == FRE_OK;
-      }
-      for (; s == FRE_OK && n >= steps; n -= steps) {
-        hipError_t e = hipGraphLaunch(*gx, st);
-        if (e != hipSuccess) s = fail(FRE_EDEVICE, "batch graph launch failed: %s", hipGetErrorString(e));
-        else done += steps;
-      }
-    };
-    replay(&B->graph_run, &B->graph_run_ok, kGraphRun);
-    replay(&B->graph, &B->graph_ok, 2);
+    if (s == FRE_OK && n >= 2) {
+      s = batch_replay(B, n & ~(int64_t)1, &done);
+      n &= 1;
+    }
     if (s == FRE_OK && n) s = one();
   }
   for (fre_lattice *L : B->slot)
@@ -1699,6 +1757,11 @@ void fre_batch_destroy(fre_batch *B) {
   for (fre_lattice *L : B->slot)
     if (L) L->batch = nullptr;
   batch_reset_graph(B);
+  for (int c = 0; c < N_BATCH_CLASSES; ++c) {
+    if (B->cls_stream[c]) (void)hipStreamDestroy(B->cls_stream[c]);
+    if (B->join[c]) (void)hipEventDestroy(B->join[c]);
+  }
+  if (B->fork) (void)hipEventDestroy(B->fork);
   delete B;
 }
 
