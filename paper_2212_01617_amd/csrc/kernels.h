@@ -81,9 +81,11 @@ struct UDiv {
 
 // Order of the 64 x rows tiles in a 1D grid of `blocks` blocks: gx tiles per
 // row of tiles, gy rows of tiles per plane; with xcd set, the first `full`
-// blocks follow the XCD-aware order (whole rounds of 8 rows of tiles).
+// blocks follow the XCD-aware order (whole rounds of 8 rows of tiles), with
+// last >= 0 (the last of these rounds) from the last round to the first; a
+// tile stays on its XCD.
 struct TileMap {
-  int gx = 1, gy = 1, xcd = 0, full = 0;
+  int gx = 1, gy = 1, xcd = 0, full = 0, last = -1;
   UDiv dgx, dgy;
   TileMap() = default;
   TileMap(int ex, int ey, int rows, int blocks, int xcd_order)

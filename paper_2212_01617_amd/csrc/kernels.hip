@@ -57,7 +57,8 @@ __device__ __forceinline__ void tile_of_block(const TileMap &T, uint32_t b, uint
   uint32_t t = b;
   if (T.xcd && b < (uint32_t)T.full) {
     const uint32_t k = b % NXCD, j = b / NXCD, jq = udiv(j, T.dgx);
-    t = (jq * NXCD + k) * gx + (j - jq * gx);
+    const uint32_t round = T.last >= 0 ? (uint32_t)T.last - jq : jq;
+    t = (round * NXCD + k) * gx + (j - jq * gx);
   }
   r = udiv(t, T.dgx);
   bx = t - r * gx;
@@ -1863,6 +1864,16 @@ static dim3 cell_block() { return dim3(BX, BY, 1); }
 static dim3 tile_grid(const Geom &G, int rows) {
   return dim3((unsigned)(((G.ex + BX - 1) / BX) * ((G.ey + rows - 1) / rows) * G.ez));
 }
+// The passes over FP32 populations run through the lattice alternately from
+// either end, by the parity of the state they read: a pass then starts with
+// the planes that the one before it touched last, part of which the 256 MB
+// Infinity Cache still holds.  A step of 256x128x128 takes 357 instead of 365
+// us, of the four-roller cell 432 instead of 449, of a ternary 256x128x128
+// lattice 598 instead of 614.  Tiles stay on their XCDs: with all blocks
+// reversed, lattices that the L2s hold from one launch to the next lost up to
+// 40% (512x256 D2Q9 11.6 -> 16.4 us).  FP16 passes measured 248 against 246 us
+// and keep one order.
+static void alternate(TileMap &t, int odd) { t.last = odd && t.full ? t.full / (8 * t.gx) - 1 : -1; }
 static int fill_blocks(int n) { return (n + 255) / 256; }
 
 template <int Q, int S>
@@ -1887,6 +1898,7 @@ static void cells_launch(const LaunchArgs &a, int odd, int tick = 0) {
   const int rows = (STAGE == ST_COLLIDE && ByProduct<S>::on) ? COLLIDE_ROWS : sh.rows;
   const dim3 grid = tile_grid(a.G, rows), block(BX, rows, 1);
   L.tm = TileMap(a.G.ex, a.G.ey, rows, (int)grid.x, sh.xcd);
+  if (S == 0 && (STAGE == ST_COLLIDE || STAGE == ST_COMBINE)) alternate(L.tm, odd);
   if constexpr (S == 1 && STAGE == ST_COLLIDE) {
     if (a.ctr) {  // stochastic rounding
       if (odd) k_cells<Q, S, STAGE, 1, true><<<grid, block, 0, a.stream>>>(L);
@@ -1927,6 +1939,7 @@ static void collide_2d_launch(const LaunchArgs &a, int odd) {
   LatView<9, S> L = view_of_args<9, S>(a);
   const dim3 grid = tile_grid(a.G, COLLIDE_ROWS), block = cell_block();
   L.tm = TileMap(a.G.ex, a.G.ey, COLLIDE_ROWS, (int)grid.x, a.shape[SHAPE_COLLIDE].xcd);
+  if (S == 0) alternate(L.tm, odd);
   if constexpr (S == 1) {
     if (a.ctr) {  // stochastic rounding
       if (odd) k_collide_2d<S, 1, true><<<grid, block, 0, a.stream>>>(L);
@@ -2115,16 +2128,17 @@ static T3View<Q> t3_view(const LaunchArgs &a) {
 // cache lines that odd-parity streaming shares across a tile edge are
 // fetched once)
 template <int Q>
-static dim3 t3_tiles(const LaunchArgs &a, T3View<Q> &T) {
+static dim3 t3_tiles(const LaunchArgs &a, T3View<Q> &T, int odd) {
   const dim3 grid = tile_grid(a.G, BY);
   T.tm = TileMap(a.G.ex, a.G.ey, BY, (int)grid.x, 1);
+  alternate(T.tm, odd);
   return grid;
 }
 
 template <int Q>
 static void t3_couple(const LaunchArgs &a, int odd) {
   T3View<Q> T = t3_view<Q>(a);
-  const dim3 tiles = t3_tiles<Q>(a, T);
+  const dim3 tiles = t3_tiles<Q>(a, T, odd);
   k3_moments<Q><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
   const bool fills = a.n_fill && !a.G.flat;
   if (fills) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
@@ -2136,7 +2150,7 @@ template <int Q>
 static void t3_step(const LaunchArgs &a, int odd) {
   t3_couple<Q>(a, odd);
   T3View<Q> T = t3_view<Q>(a);
-  const dim3 tiles = t3_tiles<Q>(a, T);
+  const dim3 tiles = t3_tiles<Q>(a, T, odd);
   if (odd) k3_collide<Q, 1><<<tiles, cell_block(), 0, a.stream>>>(T);
   else k3_collide<Q, 0><<<tiles, cell_block(), 0, a.stream>>>(T);
 }
@@ -2149,11 +2163,11 @@ void launch_step3(const LaunchArgs &a, int odd) {
 void launch_moments3(const LaunchArgs &a, int odd) {
   if (a.q == 9) {
     T3View<9> T = t3_view<9>(a);
-    const dim3 tiles = t3_tiles<9>(a, T);
+    const dim3 tiles = t3_tiles<9>(a, T, odd);
     k3_moments<9><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
   } else {
     T3View<19> T = t3_view<19>(a);
-    const dim3 tiles = t3_tiles<19>(a, T);
+    const dim3 tiles = t3_tiles<19>(a, T, odd);
     k3_moments<19><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
   }
 }
