@@ -34,7 +34,7 @@ constexpr int BX = 64, BY = 4;
 
 __device__ __forceinline__ bool cell_of_thread(const Geom &G, int &x, int &y, int &z, long long &c) {
   x = blockIdx.x * BX + threadIdx.x;
-  y = blockIdx.y * BY + threadIdx.y;
+  y = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * BY + threadIdx.y));  // a wave is one row
   z = blockIdx.z;
   if (x >= G.ex || y >= G.ey) return false;
   c = (long long)x + (long long)G.px * ((long long)y + (long long)G.ey * z);
@@ -233,17 +233,36 @@ template <class V> struct DirBits {
   __device__ static uint32_t solid_sources(uint32_t bits) { return ((bits >> 1) & ODD) | ((bits << 1) & EVEN); }
 };
 
-// Neighbour word of cell c.  A 64-cell row segment flagged all-fluid (every
-// cell fluid, every neighbour fluid) gives 0 without reading nbm: each wave
+// The component of direction i along the axis of the flat walls (the last one).
+template <class V> __host__ __device__ constexpr int cn(int i) { return V::D == 3 ? V::cz(i) : V::cy(i); }
+__device__ __forceinline__ int wall_layer(const Geom &G, int D) { return (D == 3 ? G.ez : G.ey) - 2; }
+
+// Neighbour word of a cell.  A plain lattice's follows from the cell's place
+// between the walls, the same for a whole wave and without a load before the
+// wave can start.  Else, in a 64-cell row segment flagged all-fluid (every
+// cell fluid, every neighbour fluid), it is 0 without reading nbm: each wave
 // of the single-lattice cell kernels covers exactly one segment, so the flag
 // is one scalar load per wave in place of 256 bytes of neighbour words.
-template <int Q, int S>
-__device__ __forceinline__ uint32_t nb_word(const LatView<Q, S> &L, long long c) {
-  if (L.segf) {
-    const uint32_t sg = __builtin_amdgcn_readfirstlane((uint32_t)(c >> 6));
-    if (L.segf[sg]) return 0u;
+template <class V>
+__device__ __forceinline__ uint32_t nb_word(const Geom &G, const uint32_t *nbm, const uint8_t *segf, int y, int z,
+                                            long long c) {
+  if (G.plain) {
+    if (!G.flat) return 0u;
+    const int n = V::D == 3 ? z : y, top = wall_layer(G, V::D);
+    constexpr int ax = V::D == 3 ? 2 : 1;
+    constexpr uint32_t low = DirBits<V>::with(ax, -1), high = DirBits<V>::with(ax, 1);
+    if (n < 1 || n > top) return NB_SELF_SOLID;
+    return (n == 1 ? low : 0u) | (n == top ? high : 0u);
   }
-  return L.nbm[c];
+  if (segf) {
+    const uint32_t sg = __builtin_amdgcn_readfirstlane((uint32_t)(c >> 6));
+    if (segf[sg]) return 0u;
+  }
+  return nbm[c];
+}
+template <int Q, int S>
+__device__ __forceinline__ uint32_t nb_word(const LatView<Q, S> &L, int y, int z, long long c) {
+  return nb_word<VSet<Q>>(L.G, L.nbm, L.segf, y, z, c);
 }
 
 // Second pass for fluid cell c: adds the unavailable sources of each group,
@@ -300,7 +319,7 @@ template <int Q, int S, int ODD>
 __device__ __forceinline__ void stage_moments(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, c);
+  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float df[Q], g[Q];
@@ -339,7 +358,7 @@ __device__ __forceinline__ void stage_moments(const LatView<Q, S> &L, int x, int
 template <int Q, int S, int PAR>
 __device__ __forceinline__ void stage_combine(const LatView<Q, S> &L, int x, int y, int z) {
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, c);
+  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float2 grp[3];
@@ -400,11 +419,9 @@ __device__ __forceinline__ void fluid_mean(const float *__restrict__ X, uint32_t
 // order).  Masks, rollers
 // and walls on other axes keep the fill kernels: their ghost cells have other
 // neighbours, up to four cells from the reader.
-template <class V> __host__ __device__ constexpr int cn(int i) { return V::D == 3 ? V::cz(i) : V::cy(i); }
-// tangential components of direction i (the second is 0 in 2D)
+// The second tangential component of direction i (0 in 2D).
 template <class V> __host__ __device__ constexpr int ct1(int i) { return V::D == 3 ? V::cy(i) : 0; }
 
-__device__ __forceinline__ int wall_layer(const Geom &G, int D) { return (D == 3 ? G.ez : G.ey) - 2; }
 // whether a cell (on the last axis at n) has ghost neighbours of a flat wall
 template <class V> __device__ __forceinline__ bool by_flat_wall(const Geom &G, int y, int z) {
   const int n = V::D == 3 ? z : y;
@@ -780,6 +797,55 @@ __device__ __forceinline__ void bounce_back(const Pops<Q, S> &P, const Nbr &N, l
   }
 }
 
+// The same next to one flat wall of a plain lattice (SIDE: low or high end):
+// the links are the same for the whole wave and so is the wall's velocity, so
+// nothing is looked up and the populations are loaded all at once.
+template <int Q, int S, int ODD, int SIDE, bool WITH_G, bool SR>
+__device__ __forceinline__ void bounce_flat_side(const Pops<Q, S> &P, const Nbr &N, long long c, const Phys &ph,
+                                                 float rho, float phi, uint32_t &rs) {
+  using V = VSet<Q>;
+  constexpr int ax = V::D == 3 ? 2 : 1;
+  float f[Q], g[Q];
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    if (cn<V>(i) != SIDE) continue;
+    const long long sc = ODD ? (long long)N.template at<V>(i) : c;
+    f[i] = P.ldfc(ODD ? i : opp(i), sc);
+    g[i] = WITH_G ? P.ldgc(ODD ? i : opp(i), sc) : 0.0f;
+  }
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    if (cn<V>(i) != SIDE) continue;
+    const float *uw = ph.wall_u[ax][SIDE > 0 ? 1 : 0];
+    const float k = 6.0f * V::w(i) * (V::cx(i) * uw[0] + V::cy(i) * uw[1] + V::cz(i) * uw[2]);
+    const long long bc = ODD ? c : (long long)N.template at<V>(i);
+    P.stf(ODD ? opp(i) : i, bc, P.template round_at<SR>(f[i] - k * rho, rs));
+    if (WITH_G) P.stg(ODD ? opp(i) : i, bc, P.template round_at<SR>(g[i] - k * phi, rs));
+  }
+}
+
+// Bounce-back on the links in `bits`, by whichever of the two applies.
+template <int Q, int S, int ODD, bool WITH_G = true, bool SR = false>
+__device__ __forceinline__ void bounce(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x, int y,
+                                       int z, float rho, float phi, uint32_t &rs) {
+  using V = VSet<Q>;
+  const int n = V::D == 3 ? z : y, top = wall_layer(L.G, V::D);
+  if (L.G.plain && top > 1) {
+    // the empty statements differ, so the compiler does not share the ends of
+    // the two branches: a conversion to half shared by both would no longer
+    // fuse with its multiply-add and round as bounce_back's does
+    if (n == 1) {
+      bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs);
+      asm volatile("; low wall");
+    } else {
+      bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs);
+      asm volatile("; high wall");
+    }
+  } else {  // masks, rollers, other walls, or both flat walls at once
+    bounce_back<Q, S, ODD, WITH_G, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
+  }
+}
+
 // Force and mu_phi of a cell from the coupling field, and its populations.
 // D2Q9 loads the populations before the force (one round of latency for
 // both).  D3Q19 loads them after it: with both in flight it holds 166
@@ -852,7 +918,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
   if (!ByProduct<S>::on) {
     if (!active) return;
-    const uint32_t bits = nb_word<Q, S>(L, c);
+    const uint32_t bits = nb_word<Q, S>(L, y, z, c);
     if (bits & NB_SELF_SOLID) return;
     const Nbr N(L.G, x, y, z);
     float rho, phi;
@@ -861,7 +927,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
     float df[Q], g[Q];
     collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, nullptr,
                                     0, rho, phi, rest, rs);
-    if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
+    if (bits != 0u) bounce<Q, S, ODD, true, SR>(L, N, c, bits, x, y, z, rho, phi, rs);
     return;
   }
   __shared__ float post[2 * (Q - 1)][NT];
@@ -870,7 +936,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
   bool fluid = false;
   float2 rest = make_float2(0.0f, 0.0f);
   if (active) {
-    const uint32_t bits = nb_word<Q, S>(L, c);
+    const uint32_t bits = nb_word<Q, S>(L, y, z, c);
     fluid = !(bits & NB_SELF_SOLID);
     if (fluid) {
       const Nbr N(L.G, x, y, z);
@@ -879,7 +945,7 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
       float df[Q], g[Q];
       collide_cell<Q, S, ODD, NT>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, post,
                                   tid, rho, phi, rest, rs);
-      if (bits != 0u) bounce_back<Q, S, ODD>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
+      if (bits != 0u) bounce<Q, S, ODD>(L, N, c, bits, x, y, z, rho, phi, rs);
     }
   }
   live[tid] = fluid ? 1 : 0;
@@ -909,7 +975,7 @@ template <int Q, int S, int ODD>
 __device__ __forceinline__ void stage_pre_moments(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  if (L.nbm[c] & NB_SELF_SOLID) return;
+  if (nb_word<Q, S>(L, y, z, c) & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float drho = 0.0f;
 #pragma unroll
@@ -921,7 +987,7 @@ template <int Q, int S, int ODD>
 __device__ __forceinline__ void stage_pre_collide(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, c);
+  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   const float4 cc = L.C[c];
@@ -952,7 +1018,7 @@ __device__ __forceinline__ void stage_pre_collide(const LatView<Q, S> &L, int x,
     else L.P.stf(i, N.template at<V>(i), fs);
   }
   uint32_t rs = 0u;
-  if (bits != 0u) bounce_back<Q, S, ODD, false>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, 0.0f, rs);
+  if (bits != 0u) bounce<Q, S, ODD, false>(L, N, c, bits, x, y, z, rho, 0.0f, rs);
 }
 
 // Per-cell stages other than collide (ODD: parity of the state they read).
@@ -1047,7 +1113,7 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
     __syncthreads();
     if (tx < w && ty < h) {
       const long long c = (long long)(xlo + tx) + (long long)G.px * ((long long)(ylo + ty) + (long long)G.ey * z);
-      if (!(nb_word<Q, S>(L, c) & NB_SELF_SOLID)) {
+      if (!(nb_word<Q, S>(L, ylo + ty, z, c) & NB_SELF_SOLID)) {
         const float2 m0 = ring[sc][ty + 1][tx + 1];
         float lr, lp;
         laplacians<Q>([&](int i) {
@@ -1201,8 +1267,8 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
     float(*tile)[NT] = nullptr;
     if constexpr (BP) tile = post;
     collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple, df, g, L.ph, tile, tid, rho, phi, rest, rs);
-    const uint32_t bits = G.flat && (y == 1 || y == top) ? L.nbm[c] : 0u;
-    if (bits != 0u) bounce_back<Q, S, ODD, true, SR>(L.P, N, c, bits, L.mask, G, L.ph, x, y, 0, rho, phi, rs);
+    const uint32_t bits = nb_word<Q, S>(L, y, 0, c);
+    if (bits != 0u) bounce<Q, S, ODD, true, SR>(L, N, c, bits, x, y, 0, rho, phi, rs);
   }
   if constexpr (BP) {
     live[tid] = fluid ? 1 : 0;
@@ -1240,7 +1306,8 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_cells(char *base, const 
   for (int w = blockIdx.x; w < n; w += gridDim.x) {
     const int4 it = work[start + w];
     const LatView<Q, S> L = view_of<Q, S>(base, inst[it.x]);
-    const int x = it.y * BX + threadIdx.x, y = it.z * (int)blockDim.y + threadIdx.y, z = it.w;
+    const int x = it.y * BX + threadIdx.x, z = it.w;
+    const int y = __builtin_amdgcn_readfirstlane(it.z * (int)blockDim.y + (int)threadIdx.y);
     const bool in = x < L.G.ex && y < L.G.ey;
     if (STAGE == ST_COLLIDE) {
       stage_collide<Q, S, ODD>(L, x, y, z, in);
@@ -1559,7 +1626,7 @@ __global__ __launch_bounds__(BX *BY) void k3_moments(T3View<Q> T, int odd) {
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  if (T.nbm[c] & NB_SELF_SOLID) return;
+  if (nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c) & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   float dr = 0.0f, ph = 0.0f, ps = 0.0f;
 #pragma unroll
@@ -1627,7 +1694,7 @@ __global__ __launch_bounds__(BX *BY) void k3_potential(T3View<Q> T) {
   int x, y, z;
   long long c;
   if (!cell_of_thread(T.G, x, y, z, c)) return;
-  if (T.nbm[c] & NB_SELF_SOLID) return;
+  if (nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c) & NB_SELF_SOLID) return;
   t3_potential_at<Q, false>(T, Nbr(T.G, x, y, z), x, y, z, c);
 }
 
@@ -1710,7 +1777,7 @@ __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  const uint32_t bits = T.nbm[c];
+  const uint32_t bits = nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   float F[3], mu_phi, mu_psi;
