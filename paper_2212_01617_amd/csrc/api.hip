@@ -58,7 +58,7 @@ struct Plan {
   int off[3];
   int px;          // row pitch: ext[0] rounded up to a multiple of 64
   long long ncell;  // px * ext[1] * ext[2]
-  size_t o_f, o_g, o_g0, o_h, o_h0, o_ctr, o_mask, o_nbm, o_segf, o_M, o_C, o_CM, o_P0, o_PU, o_PD, o_XE, o_AUX, o_fill, o_part, total;
+  size_t o_f, o_g, o_g0, o_h, o_h0, o_ctr, o_mask, o_nbm, o_segf, o_M, o_C, o_CM, o_P0, o_PU, o_PD, o_XE, o_P3, o_XE3, o_AUX, o_fill, o_part, total;
 };
 
 fre_status validate(const fre_params *p) {
@@ -156,7 +156,7 @@ Plan make_plan(const fre_params *p) {
   P.o_C = take((size_t)P.ncell * 16);
   P.o_CM = t3 ? take((size_t)P.ncell * 8) : 0;
   // FP32: first-pass moment sums of the collide (same plane; below and above
-  // in 3D); the ternary step has no by-product moments
+  // in 3D)
   const bool bp = p->storage == FRE_FP32 && !t3;
   P.o_P0 = bp ? take((size_t)P.ncell * 8) : 0;
   P.o_PU = bp && P.q == 19 ? take((size_t)P.ncell * 8) : 0;
@@ -164,6 +164,9 @@ Plan make_plan(const fre_params *p) {
   // FP32: per 64-cell row segment, the post-collision (f, g) of the
   // populations that leave it through its first and last column
   P.o_XE = bp ? take((size_t)(P.ncell / 64) * 2 * (P.q == 19 ? 5 : 3) * 8) : 0;
+  // ternary: the same for three populations, a float per cell and group
+  P.o_P3 = t3 ? take((size_t)P.ncell * 4 * (P.q == 19 ? 9 : 3)) : 0;
+  P.o_XE3 = t3 ? take((size_t)(P.ncell / 64) * 2 * (P.q == 19 ? 5 : 3) * 12) : 0;
   P.o_AUX = take((size_t)P.ncell * 16);
   P.o_fill = take((size_t)P.ncell * 4);
   P.o_part = take((size_t)reduce_blocks() * 8 * sizeof(double));
@@ -383,6 +386,8 @@ void bind_args(fre_lattice *L) {
   a.h = P.o_h ? L->base + P.o_h : nullptr;
   a.h0l = P.o_h0 ? (__half *)(L->base + P.o_h0) : nullptr;
   a.CM = P.o_CM ? (float2 *)(L->base + P.o_CM) : nullptr;
+  a.P3 = P.o_P3 ? (float *)(L->base + P.o_P3) : nullptr;
+  a.XE3 = P.o_XE3 ? (float *)(L->base + P.o_XE3) : nullptr;
   a.fill_list = (int *)(L->base + P.o_fill);
   a.n_fill = (int)L->fill_host.size();
 }
@@ -404,8 +409,7 @@ fre_status observe(fre_lattice *L) {
 
 // M of the current state, without the coupling fields.
 fre_status moments_now(fre_lattice *L) {
-  if (L->a.ternary) launch_moments3(L->a, (int)(L->t & 1));
-  else if (!uses_by_product(L->a)) launch_moments(L->a, (int)(L->t & 1));  // else M is valid
+  if (!uses_by_product(L->a)) launch_moments(L->a, (int)(L->t & 1));  // else M is valid
   HIP_TRY(hipGetLastError());
   return FRE_OK;
 }
@@ -1107,8 +1111,9 @@ fre_status fre_load(fre_lattice *L, const void *host, size_t bytes) {
   if (s != FRE_OK) return s;
   HIP_TRY(hipMemcpyAsync(L->base + L->plan.o_f, (const uint8_t *)host + sizeof h, h.pops_bytes, hipMemcpyHostToDevice, L->a.stream));
   L->t = h.step;
-  if (!L->p.ternary) launch_moments(L->a, (int)(L->t & 1));  // M of the restored populations
-                                                            // (the ternary step makes its own)
+  // M of the restored populations
+  if (L->p.ternary) launch_moments3(L->a, (int)(L->t & 1));
+  else launch_moments(L->a, (int)(L->t & 1));
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(L->a.stream));
   L->state = 0;

@@ -54,6 +54,7 @@ struct LaunchArgs {
   void *h;
   __half *h0l;
   float2 *CM;
+  float *P3, *XE3;  // first-pass moment sums and sideways populations of the collide
 };
 
 template <int Q, int S> inline Pops<Q, S> make_pops(const LaunchArgs &a);
@@ -178,7 +179,8 @@ enum PackCode : int {
 };
 void launch_pack(const LaunchArgs &a, int nx, int ny, int N, unsigned long long codes, long long g0, int n,
                  double *out);
-// Ternary lattices: the moments alone (M), one step, the observables (into AUX; C, CM current), the
+// Ternary lattices: the moments from the populations (after they are set from
+// outside; a step leaves M valid), one step, the observables (into AUX; C, CM current), the
 // equilibrium initialisation (M filled from host fields, AUX = u0) and the
 // populations of storage cells [c0, c0 + n) as [3q + 2][n] floats.
 void launch_moments3(const LaunchArgs &a, int odd);

@@ -1585,8 +1585,12 @@ __global__ __launch_bounds__(64) void k_reduce_final(const double *__restrict__ 
 // ---------------------------------------------------------------------------
 // Ternary lattices (Sec. 2.2, Remark after the mobility relation): a third
 // order parameter psi with its own population h, FP32 storage, one thread
-// per cell in each pass.  A step is k3_moments, k3_fill (M), k3_potential,
-// k3_fill (Pi), k3_collide; the arithmetic follows the binary stages, with
+// per cell in each pass.  A step is k3_fill (M), k3_potential, k3_fill (Pi),
+// k3_collide, k3_combine, the moments at t+1 being a by-product of the collide
+// as in the binary FP32 step (k3_moments runs after the populations are set
+// from outside).  At 256x128x128 a separate moments pass over the three
+// populations takes 203 us; the sums cost the collide 59 us (361 -> 420) and
+// k3_combine takes 87.  The arithmetic follows the binary stages, with
 // the potentials of chem_pot3 and the force
 //   mu_rho grad rho + mu_phi grad phi + mu_psi grad psi - grad Pi,
 //   Pi = rho mu_rho + phi mu_phi + psi mu_psi,
@@ -1606,7 +1610,13 @@ template <int Q> struct T3View {
   Phys ph;
   const int *fill;
   int n_fill;
-  TileMap tm;  // block order of k3_moments and k3_collide (64 x 4 tiles)
+  // first-pass sums of the collide: plane 3 k + p holds group k (0 DN, 1 S0,
+  // 2 UP; S0 alone in 2D) of population p (f, g, h); XE as the binary one,
+  // three values per entry
+  float *P;
+  float *XE;
+  __device__ float *group(int k, int p) const { return P + (size_t)(VSet<Q>::D == 3 ? 3 * k + p : p) * (size_t)G.ncell; }
+  TileMap tm;  // block order of k3_moments, k3_collide and k3_combine (64 x 4 tiles)
   // NT: non-temporal load, for passes that read each population once and
   // nothing else of the cell again
   template <bool NT = false>
@@ -1621,21 +1631,116 @@ __device__ __forceinline__ float ld3(const T3View<Q> &T, const float *a, const N
   return (!odd || i == 0) ? T.template ld<NT>(a, i, c) : T.template ld<NT>(a, opp(i), N.template back<V>(i));
 }
 
+// The moments from the populations alone: the additions of k3_collide and
+// k3_combine in their order (per group the available sources, then the others).
 template <int Q>
 __global__ __launch_bounds__(BX *BY) void k3_moments(T3View<Q> T, int odd) {
+  using V = VSet<Q>;
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  if (nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c) & NB_SELF_SOLID) return;
+  const uint32_t bits = nb_word<V>(T.G, T.nbm, nullptr, y, z, c);
+  if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
-  float dr = 0.0f, ph = 0.0f, ps = 0.0f;
+  const float *pop[3] = {T.f, T.g, T.h};
+  float m[3];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    dr += ld3<Q, true>(T, T.f, N, c, odd, i);
-    ph += ld3<Q, true>(T, T.g, N, c, odd, i);
-    ps += ld3<Q, true>(T, T.h, N, c, odd, i);
+  for (int p = 0; p < 3; ++p) {
+    float v[Q], grp[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = ld3<Q, true>(T, pop[p], N, c, odd, i);
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      if (available<V>(T.G, x, y, bits, i)) grp[V::cz(i) + 1] += v[i];
+#pragma unroll
+    for (int i = 1; i < Q; ++i)
+      if (!available<V>(T.G, x, y, bits, i)) grp[V::cz(i) + 1] += v[i];
+    m[p] = V::D == 2 ? grp[1] : (grp[2] + grp[1]) + grp[0];
   }
-  T.M4[c] = make_float4(dr, ph, ps, 0.0f);
+  T.M4[c] = make_float4(m[0], m[1], m[2], 0.0f);
+}
+
+// The collide's first pass for population p (as moment_sums): every thread of
+// the block, after the barrier that makes `post` whole.
+template <int Q, int NT>
+__device__ __forceinline__ void t3_sums(const T3View<Q> &T, int p, int x, int y, int z, long long c, bool active,
+                                        const float (*post)[NT], const unsigned char *live, int tid, float rest) {
+  using V = VSet<Q>;
+  if (threadIdx.x < 2 * XEdge<V>::NE) {
+    const int side = threadIdx.x >= XEdge<V>::NE ? 1 : 0, e = threadIdx.x - side * XEdge<V>::NE;
+    const int xlo = x & ~(BX - 1), xs = side ? min(xlo + BX, T.G.ex) - 1 : xlo;
+    const int st = threadIdx.y * BX + (xs - xlo);
+    if (live[st]) T.XE[(size_t)XEdge<V>::index(T.G, xs, y, z, side, e) * 3 + p] = post[XEdge<V>::dir(side, e) - 1][st];
+  }
+  if (!active) return;
+  float grp[3] = {0.0f, 0.0f + rest, 0.0f};
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    if (!in_footprint(T.G, x, y, V::cx(i), V::cy(i))) continue;
+    const int st = tid - V::cx(i) - BX * V::cy(i);
+    if (live[st]) grp[V::cz(i) + 1] += post[i - 1][st];
+  }
+  T.group(1, p)[c] = grp[1];
+  if (V::D == 3) {
+    const long long pl = (long long)T.G.px * T.G.ey;
+    int zu = z + 1, zd = z - 1;
+    if (zu == T.G.ez) zu = T.G.per[2] ? 0 : -1;
+    if (zd < 0) zd = T.G.per[2] ? T.G.ez - 1 : -1;
+    if (zu >= 0) T.group(2, p)[c + (zu - z) * pl] = grp[2];
+    if (zd >= 0) T.group(0, p)[c + (zd - z) * pl] = grp[0];
+  }
+}
+
+// Second pass after the collide (as second_pass); the state at t+1 has parity
+// `par`.
+template <int Q>
+__global__ __launch_bounds__(BX *BY) void k3_combine(T3View<Q> T, int par) {
+  using V = VSet<Q>;
+  using B = DirBits<V>;
+  int x, y, z;
+  long long c;
+  if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
+  const uint32_t bits = nb_word<V>(T.G, T.nbm, nullptr, y, z, c);
+  if (bits & NB_SELF_SOLID) return;
+  const Nbr N(T.G, x, y, z);
+  float grp[3][3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) grp[p][k] = (V::D == 3 || k == 1) ? T.group(k, p)[c] : 0.0f;
+  const int xlo = x & ~(BX - 1), ylo = (y / COLLIDE_ROWS) * COLLIDE_ROWS;
+  const uint32_t solid = B::solid_sources(bits);
+  const uint32_t xe = (x == xlo ? B::XP : 0u) | (x == min(xlo + BX, T.G.ex) - 1 ? B::XM : 0u);
+  const uint32_t ye = (y == ylo ? B::YP : 0u) | (y == min(ylo + COLLIDE_ROWS, T.G.ey) - 1 ? B::YM : 0u);
+  const uint32_t un = solid | xe | ye, side = xe & ~solid;
+  const float *pop[3] = {T.f, T.g, T.h};
+  float v[3][Q];
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    if (!((un >> i) & 1u)) continue;
+    const long long s = !par ? c : (long long)N.template back<V>(i);
+    const int slot = !par ? i : opp(i);
+    const float *from[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) from[p] = pop[p] + blk_offset<4>(Q, slot, s) / 4;
+    if (V::cx(i) != 0 && ((side >> i) & 1u)) {
+      const int sx = wrap(x - V::cx(i), T.G.ex), sy = wrap(y - V::cy(i), T.G.ey);
+      const int sz = V::D == 3 ? wrap(z - V::cz(i), T.G.ez) : 0;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) from[p] = T.XE + (size_t)XEdge<V>::index(T.G, sx, sy, sz, i) * 3 + p;
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) v[p][i] = __builtin_nontemporal_load(from[p]);
+  }
+  float m[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+#pragma unroll
+    for (int i = 1; i < Q; ++i)
+      if ((un >> i) & 1u) grp[p][V::cz(i) + 1] += v[p][i];
+    m[p] = V::D == 2 ? grp[p][1] : (grp[p][2] + grp[p][1]) + grp[p][0];
+  }
+  T.M4[c] = make_float4(m[0], m[1], m[2], 0.0f);
 }
 
 // solid cells next to fluid: (rho - 1, phi, psi) into M4 (PI = 0), or Pi into
@@ -1739,15 +1844,14 @@ __device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, int x
 
 // collision of one Cahn-Hilliard population (g or h) of a fluid cell with
 // order parameter value X, potential mu and 3 Gamma = gam3, relaxing at om;
-// rest population as hi + lo; streamed in place (AA parity ODD)
-template <int Q, int ODD>
+// v: the populations; rest population as hi + lo, returned in rest_out; streamed in place (AA
+// parity ODD), the moving populations also to post[i - 1][tid]
+template <int Q, int ODD, int NT>
 __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __half *lo, const Nbr &N, long long c,
                                                const float m[3], float inv_rho, float mmr, float mu, float gam3,
-                                               float om) {
+                                               float om, const float *v, float (*post)[NT], int tid,
+                                               float &rest_out) {
   using V = VSet<Q>;
-  float v[Q];
-#pragma unroll
-  for (int i = 0; i < Q; ++i) v[i] = ld3<Q>(T, a, N, c, ODD, i);
   float gm = 0.0f;
 #pragma unroll
   for (int i = 1; i < Q; ++i) gm += v[i];
@@ -1760,6 +1864,7 @@ __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __h
     const float eq = V::w(i) * gam3 * mu + X * (V::a(i) * cu + V::w(i) * ((4.5f * cmi * cu - 1.5f * mmr) * inv_rho));
     rest += eq;
     const float s = v[i] + om * (eq - v[i]);
+    post[i - 1][tid] = s;
     if (!ODD) T.st(a, opp(i), c, s);
     else T.st(a, i, N.template at<V>(i), s);
   }
@@ -1768,52 +1873,86 @@ __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __h
   const float tb = r0 - v[0];
   lo[c] = __float2half_rn(((v[0] - (r0 - tb)) + (t - tb)) * 0x1p24f);
   T.st(a, 0, c, r0);
+  rest_out = r0;
   return X;
 }
 
+// f, g and h in turn, through two LDS buffers of post-collision values (18 KB
+// each in 3D): the share of one population in the moments at t+1 is summed
+// while the next is collided into the other buffer, and a population is loaded
+// while the one before it is collided.
 template <int Q, int ODD>
 __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   using V = VSet<Q>;
+  constexpr int NT = BX * BY;
+  static_assert(BY == COLLIDE_ROWS, "the tile is the footprint of the sums");
+  __shared__ float post[2][Q - 1][NT];
+  __shared__ unsigned char live[NT];
   int x, y, z;
-  long long c;
-  if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  const uint32_t bits = nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c);
-  if (bits & NB_SELF_SOLID) return;
+  long long c = 0;
+  const bool in = cell_of_tile(T.G, T.tm, x, y, z, c);
+  const int tid = threadIdx.y * BX + threadIdx.x;
+  const uint32_t bits = in ? nb_word<V>(T.G, T.nbm, nullptr, y, z, c) : NB_SELF_SOLID;
+  const bool fluid = !(bits & NB_SELF_SOLID);
   const Nbr N(T.G, x, y, z);
-  float F[3], mu_phi, mu_psi;
-  t3_force<Q>(T, N, x, y, z, c, F, mu_phi, mu_psi);
-  // f: BGK with the Guo term, first moments exact as in collide_cell
-  float df[Q];
+  float m[3], inv_rho = 0.0f, mmr = 0.0f, mu_phi = 0.0f, mu_psi = 0.0f;
+  float rho = 0.0f, phi = 0.0f, psi = 0.0f, rest[3] = {0.0f, 0.0f, 0.0f}, v[Q], u[Q];
+  live[tid] = fluid ? 1 : 0;
+  if (fluid) {
+    float F[3];
+    t3_force<Q>(T, N, x, y, z, c, F, mu_phi, mu_psi);
+    // f: BGK with the Guo term, first moments exact as in collide_cell
+    float df[Q];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) df[i] = ld3<Q>(T, T.f, N, c, ODD, i);
-  float drho = 0.0f, j[3] = {0, 0, 0};
+    for (int i = 0; i < Q; ++i) df[i] = ld3<Q>(T, T.f, N, c, ODD, i);
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    drho += df[i];
-    j[0] += V::cx(i) * df[i];
-    j[1] += V::cy(i) * df[i];
-    j[2] += V::cz(i) * df[i];
+    for (int i = 0; i < Q; ++i) v[i] = ld3<Q>(T, T.g, N, c, ODD, i);
+    float drho = 0.0f, j[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      drho += df[i];
+      j[0] += V::cx(i) * df[i];
+      j[1] += V::cy(i) * df[i];
+      j[2] += V::cz(i) * df[i];
+    }
+    rho = 1.0f + drho;
+    inv_rho = 1.0f / rho;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) m[a] = j[a] + 0.5f * F[a];
+    mmr = (m[0] * m[0] + m[1] * m[1] + m[2] * m[2]) * inv_rho;
+    const float uF = (m[0] * F[0] + m[1] * F[1] + m[2] * F[2]) * inv_rho;
+    const double drho_d = (double)drho;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const float cF = V::cx(i) * F[0] + V::cy(i) * F[1] + V::cz(i) * F[2];
+      const float cm = V::cx(i) * m[0] + V::cy(i) * m[1] + V::cz(i) * m[2];
+      const float cu = cm * inv_rho;
+      const float wi = V::w(i), ai = V::a(i);
+      const float dfeq = feq_shifted(wi, ai, drho_d, cm, wi * (4.5f * cm * cu - 1.5f * mmr));
+      const float src = T.ph.guo * (ai * cF - 3.0f * wi * uF + 3.0f * ai * cu * cF);
+      const float fs = df[i] + T.ph.om_f * (dfeq - df[i]) + src;
+      if (i == 0) rest[0] = fs;
+      else post[0][i - 1][tid] = fs;
+      if (!ODD || i == 0) T.st(T.f, i == 0 ? 0 : opp(i), c, fs);
+      else T.st(T.f, i, N.template at<V>(i), fs);
+    }
   }
-  const float rho = 1.0f + drho, inv_rho = 1.0f / rho;
-  const float m[3] = {j[0] + 0.5f * F[0], j[1] + 0.5f * F[1], j[2] + 0.5f * F[2]};
-  const float mmr = (m[0] * m[0] + m[1] * m[1] + m[2] * m[2]) * inv_rho;
-  const float uF = (m[0] * F[0] + m[1] * F[1] + m[2] * F[2]) * inv_rho;
-  const double drho_d = (double)drho;
+  __syncthreads();
+  if (fluid) {
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const float cF = V::cx(i) * F[0] + V::cy(i) * F[1] + V::cz(i) * F[2];
-    const float cm = V::cx(i) * m[0] + V::cy(i) * m[1] + V::cz(i) * m[2];
-    const float cu = cm * inv_rho;
-    const float wi = V::w(i), ai = V::a(i);
-    const float dfeq = feq_shifted(wi, ai, drho_d, cm, wi * (4.5f * cm * cu - 1.5f * mmr));
-    const float src = T.ph.guo * (ai * cF - 3.0f * wi * uF + 3.0f * ai * cu * cF);
-    const float fs = df[i] + T.ph.om_f * (dfeq - df[i]) + src;
-    if (!ODD || i == 0) T.st(T.f, i == 0 ? 0 : opp(i), c, fs);
-    else T.st(T.f, i, N.template at<V>(i), fs);
+    for (int i = 0; i < Q; ++i) u[i] = ld3<Q>(T, T.h, N, c, ODD, i);
+    phi = t3_collide_ch<Q, ODD>(T, T.g, T.g0l, N, c, m, inv_rho, mmr, mu_phi, T.ph.gam3, T.ph.om_g, v, post[1], tid,
+                                rest[1]);
   }
-  const float phi = t3_collide_ch<Q, ODD>(T, T.g, T.g0l, N, c, m, inv_rho, mmr, mu_phi, T.ph.gam3, T.ph.om_g);
-  const float psi = t3_collide_ch<Q, ODD>(T, T.h, T.h0l, N, c, m, inv_rho, mmr, mu_psi, T.ph.gam3h, T.ph.om_h);
-  if (!bits) return;
+  t3_sums<Q>(T, 0, x, y, z, c, in, post[0], live, tid, rest[0]);
+  __syncthreads();
+  if (fluid)
+    psi = t3_collide_ch<Q, ODD>(T, T.h, T.h0l, N, c, m, inv_rho, mmr, mu_psi, T.ph.gam3h, T.ph.om_h, u, post[0], tid,
+                                rest[2]);
+  t3_sums<Q>(T, 1, x, y, z, c, in, post[1], live, tid, rest[1]);
+  __syncthreads();
+  t3_sums<Q>(T, 2, x, y, z, c, in, post[0], live, tid, rest[2]);
+  if (!fluid || !bits) return;
   // moving halfway bounce-back, as bounce_back() for each population
 #pragma unroll
   for (int i = 1; i < Q; ++i) {
@@ -2186,6 +2325,7 @@ static T3View<Q> t3_view(const LaunchArgs &a) {
   T.g0l = (__half *)a.g0; T.h0l = a.h0l;
   T.nbm = a.nbm; T.mask = a.mask;
   T.M4 = (float4 *)a.M; T.C4 = a.C; T.CM = a.CM; T.AUX = a.AUX;
+  T.P = a.P3; T.XE = a.XE3;
   T.G = a.G; T.ph = a.ph; T.fill = a.fill_list; T.n_fill = a.n_fill;
   return T;
 }
@@ -2202,11 +2342,10 @@ static dim3 t3_tiles(const LaunchArgs &a, T3View<Q> &T, int odd) {
   return grid;
 }
 
+// Coupling fields of the current state (M4 valid).
 template <int Q>
-static void t3_couple(const LaunchArgs &a, int odd) {
-  T3View<Q> T = t3_view<Q>(a);
-  const dim3 tiles = t3_tiles<Q>(a, T, odd);
-  k3_moments<Q><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
+static void t3_couple(const LaunchArgs &a) {
+  const T3View<Q> T = t3_view<Q>(a);
   const bool fills = a.n_fill && !a.G.flat;
   if (fills) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
   k3_potential<Q><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(T);
@@ -2215,11 +2354,13 @@ static void t3_couple(const LaunchArgs &a, int odd) {
 
 template <int Q>
 static void t3_step(const LaunchArgs &a, int odd) {
-  t3_couple<Q>(a, odd);
+  t3_couple<Q>(a);
   T3View<Q> T = t3_view<Q>(a);
   const dim3 tiles = t3_tiles<Q>(a, T, odd);
   if (odd) k3_collide<Q, 1><<<tiles, cell_block(), 0, a.stream>>>(T);
   else k3_collide<Q, 0><<<tiles, cell_block(), 0, a.stream>>>(T);
+  t3_tiles<Q>(a, T, odd ^ 1);
+  k3_combine<Q><<<tiles, cell_block(), 0, a.stream>>>(T, odd ^ 1);
 }
 
 void launch_step3(const LaunchArgs &a, int odd) {
@@ -2241,10 +2382,10 @@ void launch_moments3(const LaunchArgs &a, int odd) {
 
 void launch_observe3(const LaunchArgs &a, int odd) {
   if (a.q == 9) {
-    t3_couple<9>(a, odd);
+    t3_couple<9>(a);
     k3_observe<9><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(t3_view<9>(a), odd);
   } else {
-    t3_couple<19>(a, odd);
+    t3_couple<19>(a);
     k3_observe<19><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(t3_view<19>(a), odd);
   }
 }
@@ -2254,6 +2395,7 @@ static void t3_init(const LaunchArgs &a) {
   const T3View<Q> T = t3_view<Q>(a);
   if (a.n_fill) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
   k3_init<Q><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(T);
+  launch_moments3(a, 0);  // M of the populations just set
 }
 
 void launch_init3(const LaunchArgs &a) {
