@@ -667,7 +667,8 @@ __device__ __forceinline__ void load_collide(const Pops<Q, S> &P, const Nbr &N, 
 // rounding error of the sum kept (TwoSum, Knuth).
 //
 // couple(F, mu_phi) forms the force and the cell's mu_phi (and may load the
-// populations after it); df, g: the populations, from load_collide.
+// populations after it); df, g: the populations, from load_collide, and on
+// return the moving ones as they are stored.
 template <int Q, int S, int ODD, int NT, bool SR = false, class Couple>
 __device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, long long c, Couple couple,
                                              float *df, float *g, const Phys &ph, float (*post)[NT], int tid, float &rho_out,
@@ -717,6 +718,7 @@ __device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, 
     geq_rest += geq;
     const float gs = P.template round_at<SR>(g[i] + ph.om_g * (geq - g[i]), rs);
     if (post) post[Q - 1 + i - 1][tid] = gs;
+    g[i] = gs;
     // streamed: slot (x, opp(i)) after an even step, (x + c_i, i) after an odd one
     if (!ODD) P.stg(opp(i), c, gs);
     else P.stg(i, N.template at<V>(i), gs);
@@ -737,6 +739,7 @@ __device__ __forceinline__ void collide_cell(const Pops<Q, S> &P, const Nbr &N, 
       continue;
     }
     if (post) post[i - 1][tid] = fs;
+    df[i] = fs;
     if (!ODD) P.stf(opp(i), c, fs);
     else P.stf(i, N.template at<V>(i), fs);
     if constexpr (!SPLIT) collide_g(i);
@@ -799,19 +802,19 @@ __device__ __forceinline__ void bounce_back(const Pops<Q, S> &P, const Nbr &N, l
 
 // The same next to one flat wall of a plain lattice (SIDE: low or high end):
 // the links are the same for the whole wave and so is the wall's velocity, so
-// nothing is looked up and the populations are loaded all at once.
-template <int Q, int S, int ODD, int SIDE, bool WITH_G, bool SR>
+// nothing is looked up; get_f(i), get_g(i) give the stored populations, all
+// before the first store.
+template <int Q, int S, int ODD, int SIDE, bool WITH_G, bool SR, class GetF, class GetG>
 __device__ __forceinline__ void bounce_flat_side(const Pops<Q, S> &P, const Nbr &N, long long c, const Phys &ph,
-                                                 float rho, float phi, uint32_t &rs) {
+                                                 float rho, float phi, uint32_t &rs, GetF get_f, GetG get_g) {
   using V = VSet<Q>;
   constexpr int ax = V::D == 3 ? 2 : 1;
   float f[Q], g[Q];
 #pragma unroll
   for (int i = 1; i < Q; ++i) {
     if (cn<V>(i) != SIDE) continue;
-    const long long sc = ODD ? (long long)N.template at<V>(i) : c;
-    f[i] = P.ldfc(ODD ? i : opp(i), sc);
-    g[i] = WITH_G ? P.ldgc(ODD ? i : opp(i), sc) : 0.0f;
+    f[i] = get_f(i);
+    g[i] = WITH_G ? get_g(i) : 0.0f;
   }
 #pragma unroll
   for (int i = 1; i < Q; ++i) {
@@ -825,9 +828,9 @@ __device__ __forceinline__ void bounce_flat_side(const Pops<Q, S> &P, const Nbr 
 }
 
 // Bounce-back on the links in `bits`, by whichever of the two applies.
-template <int Q, int S, int ODD, bool WITH_G = true, bool SR = false>
-__device__ __forceinline__ void bounce(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x, int y,
-                                       int z, float rho, float phi, uint32_t &rs) {
+template <int Q, int S, int ODD, bool WITH_G, bool SR, class GetF, class GetG>
+__device__ __forceinline__ void bounce_with(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x,
+                                            int y, int z, float rho, float phi, uint32_t &rs, GetF get_f, GetG get_g) {
   using V = VSet<Q>;
   const int n = V::D == 3 ? z : y, top = wall_layer(L.G, V::D);
   if (L.G.plain && top > 1) {
@@ -835,15 +838,25 @@ __device__ __forceinline__ void bounce(const LatView<Q, S> &L, const Nbr &N, lon
     // the two branches: a conversion to half shared by both would no longer
     // fuse with its multiply-add and round as bounce_back's does
     if (n == 1) {
-      bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs);
+      bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
       asm volatile("; low wall");
     } else {
-      bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs);
+      bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
       asm volatile("; high wall");
     }
   } else {  // masks, rollers, other walls, or both flat walls at once
     bounce_back<Q, S, ODD, WITH_G, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
   }
+}
+// The stored populations read back from where the collide put them.
+template <int Q, int S, int ODD, bool WITH_G = true, bool SR = false>
+__device__ __forceinline__ void bounce(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x, int y,
+                                       int z, float rho, float phi, uint32_t &rs) {
+  using V = VSet<Q>;
+  auto at = [&](int i) { return ODD ? (long long)N.template at<V>(i) : c; };
+  bounce_with<Q, S, ODD, WITH_G, SR>(
+      L, N, c, bits, x, y, z, rho, phi, rs, [&](int i) { return L.P.ldfc(ODD ? i : opp(i), at(i)); },
+      [&](int i) { return L.P.ldgc(ODD ? i : opp(i), at(i)); });
 }
 
 // Force and mu_phi of a cell from the coupling field, and its populations.
@@ -945,7 +958,10 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
       float df[Q], g[Q];
       collide_cell<Q, S, ODD, NT>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, post,
                                   tid, rho, phi, rest, rs);
-      if (bits != 0u) bounce<Q, S, ODD>(L, N, c, bits, x, y, z, rho, phi, rs);
+      if (bits != 0u)
+        bounce_with<Q, S, ODD, true, false>(L, N, c, bits, x, y, z, rho, phi, rs,
+                                            [&](int i) { return post[i - 1][tid]; },
+                                            [&](int i) { return post[Q - 1 + i - 1][tid]; });
     }
   }
   live[tid] = fluid ? 1 : 0;
@@ -1219,7 +1235,7 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
 
   auto form_pi = [&](int r, int cc) {
     if (r >= h + PY || cc >= w + PX) return;
-    if (G.flat && (ylo + r < 1 || ylo + r > top)) return;  // ghost rows: below
+    if (G.flat && (ylo + r < 1 || ylo + r > top)) return;  // ghost rows: formed where they are read
     auto at = [&](int dx, int dy) { return mom[r + HY + dy][cc + HX + dx]; };
     const float2 m0 = at(0, 0);
     float lr, lp, mr, mp;
@@ -1232,24 +1248,6 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
   for (int r = ty - PY; r < R + PY; r += R) form_pi(r, tx);
   const int pr = tx / (2 * PX) - PY, pj = tx % (2 * PX);
   if (ty == R - 1 && pr < R + PY) form_pi(pr, pj < PX ? pj - PX : BX + pj - PX);
-  if (G.flat) {
-    __syncthreads();
-    // Pi of the ghost rows within reach of the tile, from the layer at the wall
-    auto ghosts = [&](int rg, int rs, auto sgn) {
-      constexpr int SIDE = decltype(sgn)::value;
-      if (rg < -PY || rg >= h + PY) return;
-      auto put = [&](int cc) {
-        if (cc >= w + 1) return;
-        float v;
-        ghost_mean<Q, SIDE, 1>([&](int dx, int) { return &pis[rs + PY][cc + PX + dx]; }, &v);
-        pis[rg + PY][cc + PX] = v;
-      };
-      if (ty == 0) put(tx);
-      if (ty == 1 && tx < 2) put(tx ? BX : -1);
-    };
-    ghosts(0 - ylo, 1 - ylo, std::integral_constant<int, -1>{});
-    ghosts(top + 1 - ylo, top - ylo, std::integral_constant<int, 1>{});
-  }
   __syncthreads();
 
   float2 rest = make_float2(0.0f, 0.0f);
@@ -1259,16 +1257,37 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
     auto couple = [&](float F[3], float &mu_phi) {
       const float2 m0 = mom[ty + HY][tx + HX];
       mu_phi = mus[ty][tx];
-      force_of<Q>([&](int i) {
+      const float mu_rho = coupling_mu_rho(make_float4(m0.x, m0.y, pis[ty + PY][tx + PX], mu_phi));
+      auto fetch = [&](int i) {
         const float2 m = mom[ty + HY + V::cy(i)][tx + HX + V::cx(i)];
         return make_float3(m.x, m.y, pis[ty + PY + V::cy(i)][tx + PX + V::cx(i)]);
-      }, coupling_mu_rho(make_float4(m0.x, m0.y, pis[ty + PY][tx + PX], mu_phi)), mu_phi, F);
+      };
+      if (by_flat_wall<V>(G, y, 0)) {
+        // Pi of the three ghost cells, from the cell's own row
+        float low[3], high[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          auto row = [&](int dx, int) { return &pis[ty + PY][tx + PX + a - 1 + dx]; };
+          ghost_mean<Q, -1, 1>(row, &low[a]);
+          ghost_mean<Q, 1, 1>(row, &high[a]);
+        }
+        force_of<Q>([&](int i) {
+          float3 m = fetch(i);
+          if (V::cy(i) < 0 && y == 1) m.z = low[V::cx(i) + 1];
+          if (V::cy(i) > 0 && y == top) m.z = high[V::cx(i) + 1];
+          return m;
+        }, mu_rho, mu_phi, F);
+      } else {
+        force_of<Q>(fetch, mu_rho, mu_phi, F);
+      }
     };
     float(*tile)[NT] = nullptr;
     if constexpr (BP) tile = post;
     collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple, df, g, L.ph, tile, tid, rho, phi, rest, rs);
     const uint32_t bits = nb_word<Q, S>(L, y, 0, c);
-    if (bits != 0u) bounce<Q, S, ODD, true, SR>(L, N, c, bits, x, y, 0, rho, phi, rs);
+    if (bits != 0u)
+      bounce_with<Q, S, ODD, true, SR>(L, N, c, bits, x, y, 0, rho, phi, rs, [&](int i) { return df[i]; },
+                                       [&](int i) { return g[i]; });
   }
   if constexpr (BP) {
     live[tid] = fluid ? 1 : 0;
