@@ -249,7 +249,10 @@ fre_status fre_save(fre_lattice *L, void *host, size_t bytes);
 fre_status fre_load(fre_lattice *L, const void *host, size_t bytes);
 
 /* Measurement: advance n >= 1 steps launching each kernel of the step
- * separately with HIP events around it on the bound stream (no graph), and
+ * separately with HIP events around it on the bound stream (no graph), every
+ * stage as a kernel of its own (the steps of fre_step leave out the fills
+ * between flat walls, and form the D2Q9 potential inside the collide, where
+ * there is no other solid cell; bitwise the same), and
  * write the mean duration in ms per step of each kernel into kernel_ms
  * (max_kernels >= 6 entries), indexed by kernel slot: 0 k_moments,
  * 1 k_fill_m, 2 k_potential, 3 k_fill_c, 4 k_collide, 5 k_combine.  A step

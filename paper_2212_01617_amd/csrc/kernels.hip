@@ -12,7 +12,11 @@
 // With FP32 storage the moments at t+1 are instead a by-product of k_collide
 // (partial sums on chip) completed by k_combine, so a step is k_fill_m,
 // k_potential, k_fill_c, k_collide, k_combine and k_moments runs only after
-// the populations are set from outside (initialisation, restores).
+// the populations are set from outside (initialisation, restores).  Between
+// flat walls on the last axis, with no other solid cell, the stencils form the
+// values of ghost cells themselves and no fill runs; a D2Q9 lattice without
+// solid cells (but such walls) also forms the potential inside its collide
+// (k_collide_2d).
 //
 // Streaming is in place with the AA access pattern: at even time steps a
 // cell reads and writes only its own slots (writing direction i into slot
@@ -21,8 +25,9 @@
 // update is race-free without a second population buffer.
 //
 // The coupling fields a fluid cell needs from its neighbours are packed into
-// one float4 per cell, C = (rho - 1, phi, Pi, mu_rho), with mu_phi in a
-// plane of its own; a 32-bit word per cell flags its non-fluid neighbours.
+// one float4 per cell, C = (rho - 1, phi, Pi, mu_phi) (planes of 8 bytes beside
+// M measured level: fewer bytes, twice the loads); a 32-bit word per cell flags
+// its non-fluid neighbours.
 #include <type_traits>
 
 #include "lbm_device.h"
