@@ -1148,8 +1148,17 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
   }
 }
 
+// Scalar registers of the z-marching potentials.  A wave is given them in
+// sixteens with 16 more for the trap handler, 800 a SIMD: above 80 a CU holds 7
+// of the 4-row blocks, not 8, and a grid of 8 per CU takes a second, nearly empty
+// turn (88 registers: 310 us at 512x256x256 and 46 in the four-roller cell,
+// against 247 and 38 with 76; capped, a step at 512x256x256 takes 2855 instead
+// of 2897 us FP32 and 2042 instead of 2095 FP16).  What the cap moves to vector
+// registers costs 0.3 us on small lattices.
+constexpr int POT_SGPRS = 80;
+
 template <int Q, int S>
-__global__ __launch_bounds__(BX *MAX_ROWS) void k_potential_zm(LatView<Q, S> L, int tz) {
+__global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SGPRS))) void k_potential_zm(LatView<Q, S> L, int tz) {
   __shared__ PotRing ring;
   uint32_t ubx, ur;
   tile_of_block(L.tm, blockIdx.x, ubx, ur);
@@ -1345,7 +1354,7 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_cells(char *base, const 
 // The batch potential: z-marching columns (slot, block-x, block-y, first
 // plane) of range[2] planes each, as k_potential_zm marches them.
 template <int Q, int S>
-__global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_potential(char *base, const Inst *__restrict__ inst,
+__global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SGPRS))) void k_batch_potential(char *base, const Inst *__restrict__ inst,
                                                                const int4 *__restrict__ cols,
                                                                const int *__restrict__ range) {
   __shared__ PotRing ring;
