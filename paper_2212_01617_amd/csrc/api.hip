@@ -601,10 +601,10 @@ fre_status read_packed(fre_lattice *L, unsigned long long codes, int nc, double 
       work.notify_all();
     }
     for (int w = 0; w < nth; ++w) th[w].join();
-    if (e != hipSuccess) (void)hipStreamSynchronize(st);  // queued pieces still write the buffer
     for (hipEvent_t v : ev)
       if (v) (void)hipEventDestroy(v);
   }
+  if (e != hipSuccess) (void)hipStreamSynchronize(st);  // queued pieces still write the buffer
   pin_give(pin);
   if (e != hipSuccess) return fail(FRE_EDEVICE, "field read failed: %s", hipGetErrorString(e));
   return FRE_OK;

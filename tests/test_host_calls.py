@@ -1,0 +1,145 @@
+"""What the library's host code asks of the HIP runtime, on the CPU: the host
+side of libfrelbm linked with a runtime that logs its calls and can make them
+fail (tests/hip_stub.cpp).  No kernel runs, so only the order of launches,
+waits and events, the devices they are made on and what follows an error are
+looked at."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2212_01617_amd import build as hipbuild
+from paper_2212_01617_amd import frelbm as F
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    if not (shutil.which("hipcc") or os.path.exists("/opt/rocm/bin/hipcc")):
+        pytest.skip("hipcc not found")
+    tmp = tmp_path_factory.mktemp("host")
+    flags = ["--offload-host-only", "-O1", "-std=c++17", "-fPIC"]
+    objs, bins = [], []
+    for src in hipbuild.SOURCES:
+        o = str(tmp / src.replace(".hip", ".o"))
+        subprocess.check_call([hipbuild.hipcc(), *flags, "-c", os.path.join(hipbuild.CSRC, src), "-o", o])
+        names = subprocess.check_output(["nm", "-u", o], text=True).split()
+        bins += [n for n in names if n.startswith("__hip_fatbin")]
+        objs.append(o)
+    so = str(tmp / "libfrelbm_host.so")
+    subprocess.check_call(["g++", "-shared", "-fPIC", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", os.path.join(HERE, "hip_stub.cpp"), *objs, "-Wl,-Bsymbolic",
+                           *[f"-Wl,--defsym={b}=0" for b in bins], "-lpthread", "-o", so])
+    L = C.CDLL(so)
+    for name, res, args in F._SIGS:
+        fn = getattr(L, name)
+        fn.restype, fn.argtypes = res, args
+    L.stub_log.restype = C.c_char_p
+    L.stub_stream.restype = C.c_void_p
+    L.stub_stream.argtypes = [C.c_int, C.c_int, C.c_uint32]
+    return L
+
+
+@pytest.fixture
+def rt(host):
+    host.stub_reset()
+    r = Runtime(host)
+    yield r
+    r.close()
+
+
+class Runtime:
+    """The library on the logging runtime, with the handles a test makes."""
+
+    def __init__(self, lib):
+        self.lib, self.lats, self.bats, self.bufs = lib, [], [], []
+
+    def log(self):
+        return self.lib.stub_log().decode().split("\n")[:-1]
+
+    def clear(self):
+        self.lib.stub_clear()
+
+    def fail(self, name, nth=1):
+        self.lib.stub_fail(name.encode(), nth)
+
+    def buffer(self, n):
+        a = np.zeros(n + 256, np.uint8)
+        self.bufs.append(a)
+        return a.ctypes.data + (-a.ctypes.data) % 256
+
+    def stream(self, dev=0, prio=0, mask=0xFFFFFFFF):
+        return C.c_void_p(self.lib.stub_stream(dev, prio, mask))
+
+    def params(self, shape, kind=1, storage=0, rollers=False, **kw):
+        axis = 1 if kind == 0 else 2
+        r = [((2.0, 2.0, 0.0), 0.001, 2, 1.0)] if rollers else []
+        return F.make_params(kind, shape, storage=storage, bc=tuple(int(a == axis) for a in range(3)), rollers=r,
+                             A=0.04, kappa=0.09, **kw)
+
+    def lattice(self, shape, kind=1, storage=0, stream=None, rollers=False):
+        p = self.params(shape, kind, storage, rollers)
+        n = C.c_size_t()
+        assert self.lib.fre_footprint(C.byref(p), C.byref(n)) == 0
+        N = shape[0] * shape[1] * shape[2]
+        phi = np.zeros(N)
+        mask = np.zeros(N, np.uint8)
+        if rollers:
+            mask[N // 2] = 2
+        h = C.c_void_p()
+        assert self.lib.fre_lattice_init(C.byref(p), self.buffer(n.value), n.value, stream or self.stream(),
+                                         phi.ctypes.data, None, None, mask.ctypes.data if rollers else None,
+                                         C.byref(h)) == 0
+        self.lats.append(h)
+        return h
+
+    def read(self, h, n_doubles, field=F.FRE_F_PHI):
+        out = np.zeros(n_doubles)
+        return self.lib.fre_read_moments(h, field, out.ctypes.data, n_doubles)
+
+    def batch(self, members, stream=None):
+        n, B = C.c_size_t(), C.c_void_p()
+        assert self.lib.fre_batch_footprint(8, 4096, 4096, C.byref(n)) == 0
+        st = stream or self.stream()
+        assert self.lib.fre_batch_create(self.buffer(n.value), n.value, st, 8, 4096, 4096, C.byref(B)) == 0
+        self.bats.append(B)
+        for h in members:
+            self.add(B, h)
+        return B, f"s{self.stream_id(st)}"
+
+    def add(self, B, h):
+        slot = C.c_int32()
+        assert self.lib.fre_batch_add(B, h, C.byref(slot)) == 0
+        return slot.value
+
+    def stream_id(self, st):
+        return C.cast(st, C.POINTER(C.c_int * 3)).contents[2]
+
+    def steps(self, h):
+        t, s = C.c_int64(), C.c_int32()
+        assert self.lib.fre_info(h, C.byref(t), C.byref(s)) == 0
+        return t.value, s.value
+
+    def close(self):
+        for B in self.bats:
+            self.lib.fre_batch_destroy(B)
+        for h in self.lats:
+            self.lib.fre_lattice_destroy(h)
+
+
+def test_failed_short_read_waits_before_its_buffer_is_given_back(rt):
+    """Three pieces (a read that starts no thread): the second launch fails,
+    and the first piece is still being written."""
+    st = rt.stream()
+    h = rt.lattice((1024, 600, 1), kind=0, stream=st)
+    rt.clear()
+    rt.fail("hipLaunchKernel", 2)
+    assert rt.read(h, 1024 * 600) == F.FRE_EDEVICE
+    log = rt.log()
+    assert log[0].startswith("launch k_pack")
+    assert f"sync s{rt.stream_id(st)}" in log[1:]
+    assert rt.read(h, 1024 * 600) == 0
