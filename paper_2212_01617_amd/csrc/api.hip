@@ -48,6 +48,25 @@ fre_status fail(fre_status s, const char *fmt, ...) {
       return fail(FRE_EDEVICE, "%s failed: %s", #expr, hipGetErrorString(e_));      \
   } while (0)
 
+// Events and streams are made on the current device and can only be used with
+// streams of that device: the device of `st` is current while this lives.
+// (The default stream is the current device's own.)
+struct OnDeviceOf {
+  int back = -1;
+  explicit OnDeviceOf(hipStream_t st) {
+    int cur = 0;
+    hipDevice_t dev = 0;
+    if (st && hipGetDevice(&cur) == hipSuccess && hipStreamGetDevice(st, &dev) == hipSuccess && dev != cur &&
+        hipSetDevice(dev) == hipSuccess)
+      back = cur;
+  }
+  ~OnDeviceOf() {
+    if (back >= 0) (void)hipSetDevice(back);
+  }
+  OnDeviceOf(const OnDeviceOf &) = delete;
+  OnDeviceOf &operator=(const OnDeviceOf &) = delete;
+};
+
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -512,6 +531,7 @@ void lattice_gone() {
 // need) is current on the lattice's stream.  Syncs.
 fre_status read_packed(fre_lattice *L, unsigned long long codes, int nc, double *out) {
   const long long N = L->n_user, total = (long long)nc * N;
+  const OnDeviceOf device(L->a.stream);
   PinBuf pin;
   long long piece = kPackPiece;
   hipError_t e = pin_take(pin_bytes(total), &pin);
@@ -1500,6 +1520,7 @@ fre_status batch_capture(const fre_batch *B, int cls, int pairs, hipGraphExec_t 
 // present runs on the batch's stream itself.
 fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
   hipStream_t st = B->stream;
+  const OnDeviceOf device(st);
   int first = -1, others = 0;
   for (int c = 0; c < N_BATCH_CLASSES; ++c)
     if (B->classes & (1u << c)) {

@@ -143,3 +143,20 @@ def test_failed_short_read_waits_before_its_buffer_is_given_back(rt):
     assert log[0].startswith("launch k_pack")
     assert f"sync s{rt.stream_id(st)}" in log[1:]
     assert rt.read(h, 1024 * 600) == 0
+
+
+def test_reads_of_a_lattice_on_another_device(rt):
+    st = rt.stream(dev=1)
+    h = rt.lattice((1024, 1100, 1), kind=0, stream=st)
+    assert rt.read(h, 1024 * 1100) == 0, rt.lib.fre_last_error()   # five pieces: events
+    assert rt.lib.stub_current_device() == 0
+
+
+def test_steps_of_a_batch_on_another_device(rt):
+    st = rt.stream(dev=1)
+    mem = [rt.lattice((70, 9, 1), kind=0, stream=st), rt.lattice((70, 9, 8), stream=st)]
+    B, _ = rt.batch(mem, stream=st)
+    rt.clear()
+    assert rt.lib.fre_batch_step(B, 20) == 0, rt.lib.fre_last_error()
+    assert [line.split()[2] for line in rt.log() if line.startswith("newstream")] == ["dev1"]
+    assert rt.lib.stub_current_device() == 0
