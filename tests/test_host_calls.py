@@ -160,3 +160,20 @@ def test_steps_of_a_batch_on_another_device(rt):
     assert rt.lib.fre_batch_step(B, 20) == 0, rt.lib.fre_last_error()
     assert [line.split()[2] for line in rt.log() if line.startswith("newstream")] == ["dev1"]
     assert rt.lib.stub_current_device() == 0
+
+
+def graphs(log):
+    """(graph, stream) of every graph launch."""
+    return [tuple(line.split()[1::2]) for line in log if line.startswith("graph ")]
+
+
+def test_classes_of_a_batch_are_queued_in_turn(rt):
+    """Each class gets a run of steps before any gets its next one: a queue
+    filled with one class's whole call would hold the others back."""
+    B, st = rt.batch([rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8)), rt.lattice((64, 8, 8), storage=1)])
+    rt.clear()
+    assert rt.lib.fre_batch_step(B, 52) == 0      # three runs of 16 and two pairs
+    order = [s for _, s in graphs(rt.log())]
+    assert len(order) == 15 and len(set(order)) == 3
+    for k in range(0, 15, 3):
+        assert set(order[k:k + 3]) == set(order[:3])
