@@ -330,7 +330,9 @@ fre_status fre_batch_remove(fre_batch *B, int32_t slot);
  * Runs of four steps and more replay one graph per class, the classes side by
  * side on streams of the batch's own (default priority) that wait for what
  * is queued on the batch's stream and that it waits for in turn.
- * FRE_ESTATE if a member has failed. */
+ * FRE_ESTATE if a member has failed.  FRE_EDEVICE if a launch fails: the steps
+ * taken until then count (fre_info), and if they are not the same for every
+ * class, all members are put in the failed state. */
 fre_status fre_batch_step(fre_batch *B, int64_t n);
 
 /* Batch launch shape: the persistent grid of the cell kernels in blocks per

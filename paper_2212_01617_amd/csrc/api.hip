@@ -1547,31 +1547,38 @@ fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
   // waited for it before the next class started (four classes of a lattice
   // each: 64 us a step in calls of 20000 steps, 50 in calls of 2000; so, 51
   // in both).
+  // The class on the batch's stream comes first: if its first launch is
+  // refused (a stream under capture), no other stream is involved yet.
   hipError_t e = hipSuccess;
-  for (int64_t ahead = 0; ahead < n && e == hipSuccess;) {
+  int64_t ahead = 0;    // steps that every class has been given
+  bool uneven = false;  // some classes have been given a run more
+  while (ahead < n && e == hipSuccess) {
     const bool run = n - ahead >= kGraphRun;
     for (int c = first; c < N_BATCH_CLASSES && e == hipSuccess; ++c) {
       if (!(B->classes & (1u << c))) continue;
       hipStream_t cs = c == first ? st : B->cls_stream[c];
       if (c != first && ahead == 0) e = hipStreamWaitEvent(cs, B->fork, 0);
       if (e == hipSuccess) e = hipGraphLaunch(run ? B->graph_run[c] : B->graph[c], cs);
+      uneven = e != hipSuccess && c != first;
     }
-    ahead += run ? kGraphRun : 2;
+    if (e == hipSuccess) ahead += run ? kGraphRun : 2;
   }
-  for (int c = first + 1; c < N_BATCH_CLASSES && e == hipSuccess; ++c) {
+  // whatever has been launched is joined to the batch's stream, or waited for
+  for (int c = first + 1; c < N_BATCH_CLASSES && (ahead || uneven); ++c) {
     if (!(B->classes & (1u << c))) continue;
-    e = hipEventRecord(B->join[c], B->cls_stream[c]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, B->join[c], 0);
+    hipError_t j = hipEventRecord(B->join[c], B->cls_stream[c]);
+    if (j == hipSuccess) j = hipStreamWaitEvent(st, B->join[c], 0);
+    if (j == hipSuccess) continue;
+    if (e == hipSuccess) e = j;
+    if (hipStreamSynchronize(B->cls_stream[c]) != hipSuccess) uneven = true;
   }
+  *done += ahead;
   if (e != hipSuccess) {
-    // the classes are at different steps now: nothing may go on from here
-    for (int c = 0; c < N_BATCH_CLASSES; ++c)
-      if (B->cls_stream[c]) (void)hipStreamSynchronize(B->cls_stream[c]);
-    for (fre_lattice *L : B->slot)
-      if (L) L->state = 1;
+    if (uneven)  // the classes are at different steps: nothing may go on from here
+      for (fre_lattice *L : B->slot)
+        if (L) L->state = 1;
     return fail(FRE_EDEVICE, "batch graph launch failed: %s", hipGetErrorString(e));
   }
-  *done += n;
   return FRE_OK;
 }
 

@@ -177,3 +177,24 @@ def test_classes_of_a_batch_are_queued_in_turn(rt):
     assert len(order) == 15 and len(set(order)) == 3
     for k in range(0, 15, 3):
         assert set(order[k:k + 3]) == set(order[:3])
+
+
+def test_a_failed_launch_between_runs_leaves_the_members_usable(rt):
+    mem = [rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))]
+    B, st = rt.batch(mem)
+    for nth, taken in ((1, 0), (3, 16), (2, None)):
+        before = [rt.steps(h)[0] for h in mem]
+        rt.clear()
+        rt.fail("hipGraphLaunch", nth)
+        assert rt.lib.fre_batch_step(B, 48) == F.FRE_EDEVICE
+        after = [rt.steps(h) for h in mem]
+        if taken is None:     # one class is a run ahead of the other
+            assert all(s == 1 for _, s in after)
+            assert rt.lib.fre_batch_step(B, 1) == F.FRE_ESTATE
+            continue
+        # every class at the same step, and that step is reported
+        assert after == [(b + taken, 0) for b in before]
+        assert [s for _, s in graphs(rt.log())].count(st) == taken // 16
+        # what ran is joined to the batch's stream, what did not run is not
+        assert (f"wait {st}" in rt.log()) == (taken > 0)
+        assert rt.lib.fre_batch_step(B, 16) == 0
