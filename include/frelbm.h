@@ -328,8 +328,9 @@ fre_status fre_batch_remove(fre_batch *B, int32_t slot);
 
 /* Advance every member n >= 0 steps, asynchronously on the batch's stream.
  * Runs of four steps and more replay one graph per class, the classes side by
- * side on streams of the batch's own (default priority) that wait for what
- * is queued on the batch's stream and that it waits for in turn.
+ * side on streams of the batch's own that wait for what is queued on the
+ * batch's stream and that it waits for in turn; on a stream with a priority
+ * or a CU mask all of them run on that stream.
  * FRE_ESTATE if a member has failed.  FRE_EDEVICE if a launch fails: the steps
  * taken until then count (fre_info), and if they are not the same for every
  * class, all members are put in the failed state. */

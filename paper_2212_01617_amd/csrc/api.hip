@@ -273,6 +273,7 @@ struct fre_batch {
   // and the events that fork them from the batch's stream and join them
   hipStream_t cls_stream[N_BATCH_CLASSES];
   hipEvent_t fork, join[N_BATCH_CLASSES];
+  bool side;  // these streams are of the batch's stream's kind, so they are used
   int grid_cells, grid_fill;
 };
 
@@ -1490,6 +1491,17 @@ void batch_launch_step(const fre_batch *B, int odd) {
     if (B->classes & (1u << cls)) launch_batch_step(b, cls, odd);
 }
 
+// Whether work of stream a may run on b as well: the same priority and the
+// same CUs.
+bool same_kind(hipStream_t a, hipStream_t b) {
+  int pa = 0, pb = 0;
+  uint32_t ma[32] = {}, mb[32] = {};
+  const bool known = hipStreamGetPriority(a, &pa) == hipSuccess && hipStreamGetPriority(b, &pb) == hipSuccess &&
+                     hipExtStreamGetCUMask(a, 32, ma) == hipSuccess && hipExtStreamGetCUMask(b, 32, mb) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  return known && pa == pb && memcmp(ma, mb, sizeof ma) == 0;
+}
+
 // A graph of `pairs` even + odd step pairs of one class.
 fre_status batch_capture(const fre_batch *B, int cls, int pairs, hipGraphExec_t *out) {
   if (*out) return FRE_OK;
@@ -1517,7 +1529,8 @@ fre_status batch_capture(const fre_batch *B, int cls, int pairs, hipGraphExec_t 
 // and the last waves of one class run under the others.  (Two classes of 2D
 // and two of 3D lattices, eight members: the step's kernels add up to 350 us,
 // one class after another; side by side it takes about 270.)  The first class
-// present runs on the batch's stream itself.
+// present runs on the batch's stream itself, and so do all of them if that
+// stream has a priority or a CU mask, which the others would not keep to.
 fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
   hipStream_t st = B->stream;
   const OnDeviceOf device(st);
@@ -1534,11 +1547,13 @@ fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
         if (fre_status s = batch_capture(B, c, 1, &B->graph[c])) return s;
       }
       if (c != first && !B->cls_stream[c]) {
-        HIP_TRY(hipEventCreateWithFlags(&B->join[c], hipEventDisableTiming));
+        if (!B->join[c]) HIP_TRY(hipEventCreateWithFlags(&B->join[c], hipEventDisableTiming));
         HIP_TRY(hipStreamCreateWithFlags(&B->cls_stream[c], hipStreamNonBlocking));
+        B->side = same_kind(st, B->cls_stream[c]);
       }
     }
-  if (others) {
+  auto stream_of = [&](int c) { return c == first || !B->side ? st : B->cls_stream[c]; };
+  if (others && B->side) {
     if (!B->fork) HIP_TRY(hipEventCreateWithFlags(&B->fork, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(B->fork, st));
   }
@@ -1556,8 +1571,8 @@ fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
     const bool run = n - ahead >= kGraphRun;
     for (int c = first; c < N_BATCH_CLASSES && e == hipSuccess; ++c) {
       if (!(B->classes & (1u << c))) continue;
-      hipStream_t cs = c == first ? st : B->cls_stream[c];
-      if (c != first && ahead == 0) e = hipStreamWaitEvent(cs, B->fork, 0);
+      hipStream_t cs = stream_of(c);
+      if (cs != st && ahead == 0) e = hipStreamWaitEvent(cs, B->fork, 0);
       if (e == hipSuccess) e = hipGraphLaunch(run ? B->graph_run[c] : B->graph[c], cs);
       uneven = e != hipSuccess && c != first;
     }
@@ -1565,7 +1580,7 @@ fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
   }
   // whatever has been launched is joined to the batch's stream, or waited for
   for (int c = first + 1; c < N_BATCH_CLASSES && (ahead || uneven); ++c) {
-    if (!(B->classes & (1u << c))) continue;
+    if (!(B->classes & (1u << c)) || stream_of(c) == st) continue;
     hipError_t j = hipEventRecord(B->join[c], B->cls_stream[c]);
     if (j == hipSuccess) j = hipStreamWaitEvent(st, B->join[c], 0);
     if (j == hipSuccess) continue;

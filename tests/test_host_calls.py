@@ -198,3 +198,15 @@ def test_a_failed_launch_between_runs_leaves_the_members_usable(rt):
         # what ran is joined to the batch's stream, what did not run is not
         assert (f"wait {st}" in rt.log()) == (taken > 0)
         assert rt.lib.fre_batch_step(B, 16) == 0
+
+
+@pytest.mark.parametrize("how", [dict(prio=-1), dict(mask=0xFFFF)])
+def test_a_batch_keeps_to_a_stream_of_its_own_kind(rt, how):
+    """A stream with a priority, or limited to some CUs: the batch's own streams
+    would not have them."""
+    B, st = rt.batch([rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))], stream=rt.stream(**how))
+    for n in (20, 36):
+        rt.clear()
+        assert rt.lib.fre_batch_step(B, n) == 0
+        assert [s for _, s in graphs(rt.log())] == [st] * 2 * (n // 16 + n % 16 // 2)
+        assert not any(line.startswith("wait") for line in rt.log())
