@@ -295,7 +295,8 @@ void fre_lattice_destroy(fre_lattice *L);
  * class present, one persistent launch per stage of the step over a
  * device-side list of (lattice, block) work items; the list and its length
  * live in device memory, so lattices join and leave without recapturing the
- * batch's HIP graphs.  A lattice advanced inside a batch takes exactly the
+ * batch's HIP graphs (a class's are captured anew when its first lattice with
+ * solid cells to fill joins or its last one leaves).  A lattice advanced inside a batch takes exactly the
  * arithmetic it takes alone (bitwise the same populations).
  * ------------------------------------------------------------------------- */
 

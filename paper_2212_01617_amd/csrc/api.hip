@@ -1364,14 +1364,16 @@ Inst inst_of(const fre_lattice *L, const void *base) {
   return I;
 }
 
-// As reset_graph: the batch's queued graph launches finish first.
-void batch_reset_graph(fre_batch *B) {
-  bool any = false;
-  for (int c = 0; c < N_BATCH_CLASSES; ++c) any = any || B->graph[c] || B->graph_run[c];
-  if (any) (void)hipStreamSynchronize(B->stream);
+// As reset_graph: the batch's queued graph launches finish first.  Drops the
+// graphs of the classes in `of`.
+void batch_reset_graph(fre_batch *B, unsigned of = ~0u) {
+  bool waited = false;
   for (int c = 0; c < N_BATCH_CLASSES; ++c)
     for (hipGraphExec_t *g : {&B->graph[c], &B->graph_run[c]}) {
-      if (*g) (void)hipGraphExecDestroy(*g);
+      if (!*g || !(of & (1u << c))) continue;
+      if (!waited) (void)hipStreamSynchronize(B->stream);
+      waited = true;
+      (void)hipGraphExecDestroy(*g);
       *g = nullptr;
     }
 }
@@ -1461,8 +1463,9 @@ fre_status batch_rebuild(fre_batch *B) {
     HIP_TRY(hipMemcpyAsync(B->d_fill, B->h_fill.data(), B->h_fill.size() * sizeof(int2), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipMemcpyAsync(B->d_range, B->h_range.data(), BATCH_RANGE * N_BATCH_CLASSES * sizeof(int), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipStreamSynchronize(B->stream));
-  // the graph launches one sequence per class, with or without fills
-  if (classes != B->classes || fills != B->fills) batch_reset_graph(B);
+  // a class's graphs launch one sequence, with or without fills, over lists whose
+  // lengths they read in device memory: they stay valid while it is absent
+  batch_reset_graph(B, fills ^ B->fills);
   B->classes = classes;
   B->fills = fills;
   return FRE_OK;
@@ -1669,7 +1672,6 @@ fre_status fre_batch_add(fre_batch *B, fre_lattice *L, int32_t *slot) {
   // one step on its own first (the same arithmetic as inside the batch)
   if (members == 0) {
     B->parity = (int)(L->t & 1);
-    batch_reset_graph(B);
   } else if ((int)(L->t & 1) != B->parity) {
     fre_status s = fre_step(L, 1);
     if (s != FRE_OK) return s;

@@ -54,3 +54,49 @@ def test_consecutive_runs_equal_solo(present):
         for a, b in zip(L.populations(), S.populations()):
             assert np.array_equal(a, b)
     B.close()
+
+
+@pytest.mark.parametrize("kind,shape", [(0, (70, 33, 1)), (1, (66, 12, 9))])
+@pytest.mark.parametrize("storage", [0, 1])
+def test_roller_lattice_joins_and_leaves_a_class_of_flat_walls(kind, shape, storage):
+    """The class's fills run for the roller lattice alone, from when it joins
+    until it leaves; the member between flat walls never notices."""
+    nx, ny, nz = shape
+    mask = np.zeros((nz, ny, nx), np.uint8)
+    mask[:, 2:5, 10:13] = 2
+    rp = F.make_params(kind, shape, storage=storage, rollers=[((11.0, 3.0, 0.0), 0.002, 2, 2.0)], A=0.04, kappa=0.09)
+    phi0, _, _ = case_inputs(kind, shape, radius=5, xi=1.5, seed=3)
+
+    def roller():
+        return F.Lattice(rp, phi0, mask=mask, stream=torch.cuda.Stream())
+
+    flat, rol = _make(kind, shape, storage), roller()
+    sflat, srol = _make(kind, shape, storage), roller()
+    needs = [F.Batch.needs(L) for L in (flat, rol)]
+    B = F.Batch(2, sum(w for w, _ in needs), sum(f for _, f in needs))
+
+    def same(*pairs):
+        for L, S in pairs:
+            assert L.info()[0] == S.info()[0]
+            for a, b in zip(L.populations(), S.populations()):
+                assert np.isfinite(a).all() and np.array_equal(a, b)
+
+    B.add(flat)
+    B.step(22)                 # a run of 16 steps and pairs: both graphs
+    sflat.step(22)
+    same((flat, sflat))
+    slot = B.add(rol)
+    B.step(22)
+    sflat.step(22)
+    srol.step(22)
+    same((flat, sflat), (rol, srol))
+    B.remove(slot)
+    B.step(22)
+    sflat.step(22)
+    same((flat, sflat), (rol, srol))
+    B.add(rol)
+    B.step(22)
+    sflat.step(22)
+    srol.step(22)
+    same((flat, sflat), (rol, srol))
+    B.close()

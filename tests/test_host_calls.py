@@ -210,3 +210,32 @@ def test_a_batch_keeps_to_a_stream_of_its_own_kind(rt, how):
         assert rt.lib.fre_batch_step(B, n) == 0
         assert [s for _, s in graphs(rt.log())] == [st] * 2 * (n // 16 + n % 16 // 2)
         assert not any(line.startswith("wait") for line in rt.log())
+
+
+def test_members_that_join_or_leave_recapture_only_their_class(rt):
+    flat2, flat3 = rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))
+    B, _ = rt.batch([flat2, flat3])
+
+    def captures(n=18):
+        rt.clear()
+        assert rt.lib.fre_batch_step(B, n) == 0
+        return [line.split()[2:] for line in rt.log() if line.startswith("instantiate")]
+
+    assert len(captures()) == 4                     # a run and a pair for each class
+    assert captures() == []
+    slot = rt.add(B, rt.lattice((40, 9, 8)))        # another one of the same kind
+    assert captures() == []
+    roller = rt.add(B, rt.lattice((24, 12, 8), rollers=True))   # its class needs fills now
+    new = captures()
+    assert len(new) == 2 and all("k_batch_fill" in g for g in new)
+    assert rt.lib.fre_batch_remove(B, slot) == 0 and captures() == []
+    assert rt.lib.fre_batch_remove(B, roller) == 0
+    new = captures()
+    assert len(new) == 2 and not any("k_batch_fill" in g for g in new)
+    half = rt.add(B, rt.lattice((70, 9, 8), storage=1))         # a class more
+    assert len(captures()) == 2
+    assert rt.lib.fre_batch_remove(B, half) == 0 and captures() == []
+    for k in range(2):                              # empty, and filled again
+        assert rt.lib.fre_batch_remove(B, k) == 0
+    rt.add(B, flat2)
+    assert captures() == []
