@@ -268,7 +268,8 @@ const char *fre_kernel_name(int32_t k);
  * for the moments pass (k_moments, or k_combine with FP32 storage),
  * k_potential and k_collide in that order: rows of 64 cells per thread block
  * (1, 2, 4 or 8; with FP32 storage k_collide always 4, its tile being the
- * footprint of its on-chip moment sums) and xcd = 1 for the XCD-aware block
+ * footprint of its on-chip moment sums; FP16 D2Q9 lattices without solid cells
+ * step in tiles of 4 rows whatever is set) and xcd = 1 for the XCD-aware block
  * order (0: plain order).  A shape decides only which thread updates which
  * cell, never the arithmetic: results are bitwise the same under every
  * shape.  Default {4, 1} for all three.  Set syncs the bound stream;
@@ -278,7 +279,11 @@ fre_status fre_get_launch_shape(const fre_lattice *L, int32_t cfg[6]);
 
 /* Autotuner: times each of the 8 candidate shapes (rows 1, 2, 4, 8 x xcd
  * 0, 1) over n (rounded up to even, 2 <= n <= 10000) individually launched
- * steps per candidate and keeps, for each of the three kernels, the fastest.
+ * steps per candidate, with the kernels that fre_step launches, and keeps, for
+ * each of the three kernels, the fastest.  A D2Q9 lattice without solid cells
+ * forms the potential inside its collide, in tiles of 4 rows: only the block
+ * order of that kernel is chosen, the shape of k_potential (which reads still
+ * use) stays, and its time reads -1.
  * The lattice state (populations, step count) is copied to host memory
  * before and restored after, so tuning leaves the run where it was.
  * cfg_out (may be NULL) receives the chosen shapes, stage_ms (may be NULL,

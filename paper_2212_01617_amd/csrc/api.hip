@@ -1145,9 +1145,10 @@ fre_status fre_load(fre_lattice *L, const void *host, size_t bytes) {
 
 namespace {
 
-// Mean duration (ms) of each kernel of the step over n individually launched
-// steps, from HIP events recorded on the lattice's stream around every launch.
-fre_status time_kernels(fre_lattice *L, int64_t n, double *kernel_ms) {
+// Mean duration (ms) of each stage of the step as `a` launches it, over n
+// individually launched steps of L, from HIP events recorded on the lattice's
+// stream around every stage.
+fre_status time_kernels(fre_lattice *L, const LaunchArgs &a, int64_t n, double *kernel_ms) {
   const int K = step_kernel_count();
   int slot[8];
   const int nslot = step_kernel_slots(L->a, slot);
@@ -1155,13 +1156,9 @@ fre_status time_kernels(fre_lattice *L, int64_t n, double *kernel_ms) {
   for (auto &e : ev) HIP_TRY(hipEventCreate(&e));
   for (int k = 0; k < nslot; ++k) kernel_ms[k] = -1.0;  // slots this class does not launch
   for (int k = 0; k < K; ++k) kernel_ms[slot[k]] = 0.0;
-  // every stage as a launch of its own: the solid fills too, which the steps
-  // of a lattice between flat walls form inside the other kernels
-  LaunchArgs staged = L->a;
-  staged.G.flat = staged.G.plain = 0;
   fre_status st = FRE_OK;
   for (int64_t s = 0; s < n; ++s) {
-    launch_step_events(staged, (int)(L->t & 1), &ev[(size_t)s * (K + 1)]);
+    launch_step_events(a, (int)(L->t & 1), &ev[(size_t)s * (K + 1)]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { st = fail(FRE_EDEVICE, "launch failed: %s", hipGetErrorString(e)); break; }
     L->t += 1;
@@ -1227,7 +1224,11 @@ fre_status fre_profile_step(fre_lattice *L, int64_t n, double *kernel_ms, int32_
   if (L->p.ternary) return fail(FRE_EINVAL, "per-kernel profiling is not available for ternary lattices");
   if (max_kernels < K) return fail(FRE_EINVAL, "kernel_ms needs %d entries", K);
   if (L->batch) return fail(FRE_ESTATE, "lattice is a batch member: profile it alone");
-  fre_status st = time_kernels(L, n, kernel_ms);
+  // every stage as a launch of its own: also those that the steps of a lattice
+  // without solid cells form inside the other kernels
+  LaunchArgs staged = L->a;
+  staged.G.flat = staged.G.plain = 0;
+  fre_status st = time_kernels(L, staged, n, kernel_ms);
   *n_kernels = K;
   return st;
 }
@@ -1272,14 +1273,17 @@ fre_status fre_autotune(fre_lattice *L, int64_t n, int32_t cfg_out[6], double st
   double best[N_SHAPES] = {1e300, 1e300, 1e300};
   Shape pick[N_SHAPES] = {saved[0], saved[1], saved[2]};
   double ms[16];
+  const bool fused = forms_potential(L->a);
   for (const Shape &c : kCandidates) {
     for (int k = 0; k < N_SHAPES; ++k) L->a.shape[k] = c;
-    s = time_kernels(L, 2, ms);  // warm-up
-    if (s == FRE_OK) s = time_kernels(L, n, ms);
+    s = time_kernels(L, L->a, 2, ms);  // warm-up
+    if (s == FRE_OK) s = time_kernels(L, L->a, n, ms);
     if (s != FRE_OK) break;
     for (int k = 0; k < N_SHAPES; ++k) {
-      // the by-product collide runs COLLIDE_ROWS rows whatever the shape says
-      if (k == SHAPE_COLLIDE && uses_by_product(L->a) && c.rows != COLLIDE_ROWS) continue;
+      // the by-product collide and k_collide_2d run COLLIDE_ROWS rows whatever
+      // the shape says, and with the latter no k_potential runs
+      if (k == SHAPE_COLLIDE && (uses_by_product(L->a) || fused) && c.rows != COLLIDE_ROWS) continue;
+      if (k == SHAPE_POTENTIAL && fused) continue;
       const double t = ms[stage_slot(L, k)];
       if (t < best[k]) { best[k] = t; pick[k] = c; }
     }
@@ -1291,7 +1295,7 @@ fre_status fre_autotune(fre_lattice *L, int64_t n, int32_t cfg_out[6], double st
   if (r != FRE_OK) return r;
   if (cfg_out) fre_get_launch_shape(L, cfg_out);
   if (stage_ms)
-    for (int k = 0; k < N_SHAPES; ++k) stage_ms[k] = best[k];
+    for (int k = 0; k < N_SHAPES; ++k) stage_ms[k] = k == SHAPE_POTENTIAL && fused ? -1.0 : best[k];
   return FRE_OK;
 }
 

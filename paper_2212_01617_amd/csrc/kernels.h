@@ -153,16 +153,20 @@ inline int batch_class(int q, int storage) { return (q == 19 ? 2 : 0) + storage;
 
 void launch_batch_step(const BatchArgs &b, int cls, int odd);
 void launch_step(const LaunchArgs &a, int odd);
-// A step launches 5 kernels; ev receives an event before the first and after
-// each.  The kernels are named by slot: step_kernel_name(0..5) = k_moments,
-// k_fill_m, k_potential, k_fill_c, k_collide, k_combine; step_kernel_slots
-// gives, for the lattice's class, the slot of each of its 5 launches.
+// A step has 5 stages; ev receives an event before the first and after each.
+// The stages are named by slot: step_kernel_name(0..5) = k_moments, k_fill_m,
+// k_potential, k_fill_c, k_collide, k_combine; step_kernel_slots gives, for the
+// lattice's class, the slot of each of its 5 stages.  Stages that the step
+// launches no kernel for (the fills with Geom::flat, with forms_potential also
+// the potential) have their event all the same.
 void launch_step_events(const LaunchArgs &a, int odd, hipEvent_t *ev);
 int step_kernel_count();
 int step_kernel_slots(const LaunchArgs &a, int *slot);
 const char *step_kernel_name(int k);
 void launch_moments(const LaunchArgs &a, int odd);
 bool uses_by_product(const LaunchArgs &a);
+// whether the collide forms the potential itself (k_collide_2d)
+bool forms_potential(const LaunchArgs &a);
 void launch_observe(const LaunchArgs &a, int odd);
 void launch_init(const LaunchArgs &a);
 // n (even) pre-iterations of f with u held at AUX.xyz and phi at AUX.w, then

@@ -2173,6 +2173,8 @@ static void potential_launch(const LaunchArgs &a) {
   k_potential_zm<Q, S><<<dim3((unsigned)(tiles * nch)), dim3(BX, sh.rows, 1), 0, a.stream>>>(L, tz);
 }
 
+bool forms_potential(const LaunchArgs &a) { return a.q == 9 && a.G.plain && !a.ternary; }
+
 template <int S>
 static void collide_2d_launch(const LaunchArgs &a, int odd) {
   LatView<9, S> L = view_of_args<9, S>(a);
@@ -2215,9 +2217,12 @@ static void step_seq(const LaunchArgs &a, int odd, hipEvent_t *ev) {
     moments_launch<Q, S>(a, odd, 1);  // the step's moments advance the rounding counter
     if (ev) (void)hipEventRecord(ev[k++], a.stream);
   }
-  bool fused = false;
+  const bool fused = forms_potential(a);
   if constexpr (Q == 9) {
-    if ((fused = a.G.plain)) collide_2d_launch<S>(a, odd);
+    if (fused) {
+      for (int j = 0; ev && j < 3; ++j) (void)hipEventRecord(ev[k++], a.stream);  // no fills, no k_potential
+      collide_2d_launch<S>(a, odd);
+    }
   }
   if (!fused) {
     couple_seq<Q, S>(a, ev, k);

@@ -111,3 +111,24 @@ def test_batch_shapes_bitwise_and_autotune_restores():
     for L, (fr, gr) in zip(mem, ref):
         f, g = L.populations()
         assert np.array_equal(f, fr) and np.array_equal(g, gr)
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("wall", [0, 1])
+def test_d2q9_without_solids_shapes_and_tuning(storage, wall):
+    """The collide that forms the potential: block orders are bitwise the same,
+    tuning picks one of them and leaves the run where it was."""
+    shape = (150, 41, 1)
+    phi0, _, u0 = case_inputs(0, shape, radius=8, xi=1.5, u_amp=0.005, seed=5)
+    p = F.make_params(0, shape, storage=storage, bc=(0, wall, 0), A=0.04, kappa=0.09)
+    ref = F.Lattice(p, phi0, None, u0).step(11).populations()
+    for order in (0, 1):
+        L = F.Lattice(p, phi0, None, u0, stream=torch.cuda.Stream())
+        L.set_launch_shape({"k_moments": (8, order), "k_potential": (1, 0), "k_collide": (4, order)})
+        L.step(5)
+        tuned = L.autotune(4)
+        assert L.info()[0] == 5
+        assert tuned["k_potential"] == (1, 0, -1.0) and tuned["k_collide"][0] == 4 and tuned["k_collide"][2] > 0
+        L.step(6)
+        for a, b in zip(L.populations(), ref):
+            assert np.array_equal(a, b)

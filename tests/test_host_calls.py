@@ -239,3 +239,30 @@ def test_members_that_join_or_leave_recapture_only_their_class(rt):
         assert rt.lib.fre_batch_remove(B, k) == 0
     rt.add(B, flat2)
     assert captures() == []
+
+
+def launches(log):
+    return [line.split()[1] for line in log if line.startswith("launch ")]
+
+
+@pytest.mark.parametrize("kind,shape", [(0, (70, 9, 1)), (1, (70, 9, 8))])
+@pytest.mark.parametrize("storage", [0, 1])
+def test_the_tuner_times_the_kernels_that_steps_launch(rt, kind, shape, storage):
+    h = rt.lattice(shape, kind=kind, storage=storage)
+    rt.clear()
+    assert rt.lib.fre_step(h, 2) == 0
+    step = launches(rt.log())
+    assert step.count("k_fill") == 0 and ("k_collide_2d" in step) == (kind == 0)
+    cfg, ms = (C.c_int32 * 6)(), (C.c_double * 3)()
+    rt.clear()
+    assert rt.lib.fre_autotune(h, 2, cfg, ms) == 0
+    tuned = launches(rt.log())
+    assert tuned[-1] == "k_cells"                   # M of the restored state
+    assert tuned[:-1] == step * (len(tuned) // len(step))
+    if kind == 0:     # no kernel of a step takes the potential's shape, and the tile has four rows
+        assert list(cfg[:4])[2:] == [4, 1] and ms[1] == -1.0 and cfg[4] == 4
+    assert ms[0] > 0 and ms[2] > 0
+    per, n = (C.c_double * 8)(), C.c_int32()
+    rt.clear()
+    assert rt.lib.fre_profile_step(h, 2, per, 8, C.byref(n)) == 0
+    assert launches(rt.log()).count("k_fill") == 4  # profiles keep every stage
