@@ -350,8 +350,8 @@ fre_status fre_batch_set_launch_shape(fre_batch *B, int32_t blocks_per_cu);
 fre_status fre_batch_get_launch_shape(const fre_batch *B, int32_t *blocks_per_cu);
 
 /* Batch autotuner: times the batch step over n (rounded up to even,
- * 2..10000) directly launched steps for 2, 4, 8 and 16 blocks per CU and
- * keeps the fastest.  Every member's state is copied to host memory before
+ * 2..10000) steps, taken as fre_batch_step takes them, for 2, 4, 8 and 16
+ * blocks per CU and keeps the fastest.  Every member's state is copied to host memory before
  * and restored after.  blocks_per_cu and ms_per_step (may be NULL) receive
  * the choice and its mean step time.  Syncs.  FRE_ESTATE for an empty batch
  * or a failed member. */

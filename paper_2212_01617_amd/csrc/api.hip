@@ -1604,6 +1604,30 @@ fre_status batch_replay(fre_batch *B, int64_t n, int64_t *done) {
   return FRE_OK;
 }
 
+// n >= 1 steps of every member; *done counts those taken.  The members' step
+// counts are the caller's.
+fre_status batch_advance(fre_batch *B, int64_t n, int64_t *done) {
+  auto one = [&]() -> fre_status {
+    batch_launch_step(B, B->parity);
+    HIP_TRY(hipGetLastError());
+    B->parity ^= 1;
+    ++*done;
+    return FRE_OK;
+  };
+  fre_status s = FRE_OK;
+  if (B->stream == nullptr || n < 4) {
+    for (int64_t k = 0; k < n && s == FRE_OK; ++k) s = one();
+    return s;
+  }
+  if (B->parity) { s = one(); --n; }
+  if (s == FRE_OK && n >= 2) {
+    s = batch_replay(B, n & ~(int64_t)1, done);
+    n &= 1;
+  }
+  if (s == FRE_OK && n) s = one();
+  return s;
+}
+
 }  // namespace
 
 fre_status fre_batch_footprint(int32_t max_slots, int64_t max_work, int64_t max_fill, size_t *bytes) {
@@ -1709,26 +1733,8 @@ fre_status fre_batch_step(fre_batch *B, int64_t n) {
   if (!B->classes || n == 0) return FRE_OK;
   for (fre_lattice *L : B->slot)
     if (L && L->state) return fail(FRE_ESTATE, "a member lattice is in the failed state");
-  hipStream_t st = B->stream;
   int64_t done = 0;
-  auto one = [&]() -> fre_status {
-    batch_launch_step(B, B->parity);
-    HIP_TRY(hipGetLastError());
-    B->parity ^= 1;
-    ++done;
-    return FRE_OK;
-  };
-  fre_status s = FRE_OK;
-  if (st == nullptr || n < 4) {
-    for (int64_t k = 0; k < n && s == FRE_OK; ++k) s = one();
-  } else {
-    if (B->parity) { s = one(); --n; }
-    if (s == FRE_OK && n >= 2) {
-      s = batch_replay(B, n & ~(int64_t)1, &done);
-      n &= 1;
-    }
-    if (s == FRE_OK && n) s = one();
-  }
+  const fre_status s = batch_advance(B, n, &done);
   for (fre_lattice *L : B->slot)
     if (L) L->t += done;
   return s;
@@ -1767,6 +1773,9 @@ fre_status fre_batch_autotune(fre_batch *B, int64_t n, int32_t *blocks_per_cu, d
     }
   const int parity0 = B->parity, bpc0 = B->blocks_per_cu;
   static const int kBpc[] = {2, 4, 8, 16};
+  // the steps before the timed ones capture the graphs that these replay
+  const int64_t warm = std::min<int64_t>(n, 2 * kGraphRun + n % kGraphRun);
+  const OnDeviceOf device(B->stream);
   double best = 1e300;
   int best_bpc = bpc0;
   hipEvent_t e0, e1;
@@ -1775,10 +1784,10 @@ fre_status fre_batch_autotune(fre_batch *B, int64_t n, int32_t *blocks_per_cu, d
   fre_status s = FRE_OK;
   for (int bpc : kBpc) {
     if ((s = fre_batch_set_launch_shape(B, bpc)) != FRE_OK) break;
-    int par = B->parity;
-    for (int w = 0; w < 2; ++w, par ^= 1) batch_launch_step(B, par);
+    int64_t done = 0;
+    if ((s = batch_advance(B, warm, &done)) != FRE_OK) break;
     (void)hipEventRecord(e0, B->stream);
-    for (int64_t k = 0; k < n; ++k, par ^= 1) batch_launch_step(B, par);
+    if ((s = batch_advance(B, n, &done)) != FRE_OK) break;
     (void)hipEventRecord(e1, B->stream);
     hipError_t e = hipStreamSynchronize(B->stream);
     if (e == hipSuccess) e = hipGetLastError();
@@ -1789,10 +1798,12 @@ fre_status fre_batch_autotune(fre_batch *B, int64_t n, int32_t *blocks_per_cu, d
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  (void)hipStreamSynchronize(B->stream);  // after an error steps may still be queued
   for (size_t k = 0; k < B->slot.size(); ++k)
     if (B->slot[k]) {
       fre_status r = restore(B->slot[k], hs[k]);
-      if (r != FRE_OK && s == FRE_OK) s = r;
+      if (r == FRE_OK) B->slot[k]->state = 0;
+      else if (s == FRE_OK) s = r;
     }
   B->parity = parity0;
   fre_status r = fre_batch_set_launch_shape(B, s == FRE_OK ? best_bpc : bpc0);

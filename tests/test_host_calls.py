@@ -266,3 +266,17 @@ def test_the_tuner_times_the_kernels_that_steps_launch(rt, kind, shape, storage)
     rt.clear()
     assert rt.lib.fre_profile_step(h, 2, per, 8, C.byref(n)) == 0
     assert launches(rt.log()).count("k_fill") == 4  # profiles keep every stage
+
+
+def test_the_batch_tuner_times_steps_as_the_batch_takes_them(rt):
+    B, st = rt.batch([rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))])
+    bpc, ms = C.c_int32(), C.c_double()
+    rt.clear()
+    assert rt.lib.fre_batch_autotune(B, 32, C.byref(bpc), C.byref(ms)) == 0
+    log = rt.log()
+    assert not any(k.startswith("k_batch") for k in launches(log))
+    # every candidate: a run that captures, then the timed one, side by side
+    marks = [k for k, line in enumerate(log) if line == f"record {st}"]
+    assert len(graphs(log)) == 4 * 2 * 2 * 2 and len({s for _, s in graphs(log)}) == 2
+    assert marks and [rt.steps(h) for h in rt.lats] == [(0, 0), (0, 0)]
+    assert rt.lib.fre_batch_step(B, 20) == 0
