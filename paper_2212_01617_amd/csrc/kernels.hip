@@ -796,8 +796,8 @@ __device__ __forceinline__ void bounce_back(const Pops<Q, S> &P, const Nbr &N, l
     float uw[3];
     body_velocity<V>(G, ph, mask[n], x, y, z, xs, ys, zs, i, uw);
     const float k = 6.0f * V::w(i) * (V::cx(i) * uw[0] + V::cy(i) * uw[1] + V::cz(i) * uw[2]);
-    const float fb = P.template round_at<SR>(fs - k * rho, rs);
-    const float gb = P.template round_at<SR>(gs - k * phi, rs);
+    const float fb = P.template fma_at<SR>(-k, rho, fs, rs);
+    const float gb = P.template fma_at<SR>(-k, phi, gs, rs);
     const int bp = ODD ? opp(i) : i;
     const long long bc = ODD ? c : n;
     P.stf(bp, bc, fb);
@@ -827,8 +827,8 @@ __device__ __forceinline__ void bounce_flat_side(const Pops<Q, S> &P, const Nbr 
     const float *uw = ph.wall_u[ax][SIDE > 0 ? 1 : 0];
     const float k = 6.0f * V::w(i) * (V::cx(i) * uw[0] + V::cy(i) * uw[1] + V::cz(i) * uw[2]);
     const long long bc = ODD ? c : (long long)N.template at<V>(i);
-    P.stf(ODD ? opp(i) : i, bc, P.template round_at<SR>(f[i] - k * rho, rs));
-    if (WITH_G) P.stg(ODD ? opp(i) : i, bc, P.template round_at<SR>(g[i] - k * phi, rs));
+    P.stf(ODD ? opp(i) : i, bc, P.template fma_at<SR>(-k, rho, f[i], rs));
+    if (WITH_G) P.stg(ODD ? opp(i) : i, bc, P.template fma_at<SR>(-k, phi, g[i], rs));
   }
 }
 
@@ -839,16 +839,8 @@ __device__ __forceinline__ void bounce_with(const LatView<Q, S> &L, const Nbr &N
   using V = VSet<Q>;
   const int n = V::D == 3 ? z : y, top = wall_layer(L.G, V::D);
   if (L.G.plain && top > 1) {
-    // the empty statements differ, so the compiler does not share the ends of
-    // the two branches: a conversion to half shared by both would no longer
-    // fuse with its multiply-add and round as bounce_back's does
-    if (n == 1) {
-      bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
-      asm volatile("; low wall");
-    } else {
-      bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
-      asm volatile("; high wall");
-    }
+    if (n == 1) bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
+    else bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
   } else {  // masks, rollers, other walls, or both flat walls at once
     bounce_back<Q, S, ODD, WITH_G, SR>(L.P, N, c, bits, L.mask, L.G, L.ph, x, y, z, rho, phi, rs);
   }

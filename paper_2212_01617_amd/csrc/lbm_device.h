@@ -260,6 +260,16 @@ __device__ __forceinline__ float sr_half(float v, uint32_t r) {
   return copysignf(t, v);
 }
 
+// a b + c rounded to half once, by the one instruction that does so.  The plain
+// expression leaves it to the compiler whether the conversion joins the
+// multiply-add (one rounding) or follows it (two), and it decides by what else
+// shares the conversion: two forms of one formula could store different halves.
+__device__ __forceinline__ float half_fma(float a, float b, float c) {
+  uint32_t r;  // the upper 16 bits are not written
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return __half2float(__builtin_bit_cast(__half, (unsigned short)r));
+}
+
 template <int Q, int S> struct Pops;
 
 template <int Q> struct Pops<Q, 0> {
@@ -273,6 +283,9 @@ template <int Q> struct Pops<Q, 0> {
   __device__ __forceinline__ float round(float v) const { return v; }
   template <bool SR>
   __device__ __forceinline__ float round_at(float v, uint32_t &) const { return v; }
+  // the value a store keeps of a b + c
+  template <bool SR>
+  __device__ __forceinline__ float fma_at(float a, float b, float c, uint32_t &) const { return __builtin_fmaf(a, b, c); }
   __device__ __forceinline__ uint32_t step_key() const { return 0u; }
   __device__ __forceinline__ float ldg0lo(long long c) const { return __half2float(g0l[c]) * 0x1p-24f; }
   __device__ __forceinline__ void stg0lo(long long c, float lo) const { g0l[c] = __float2half_rn(lo * 0x1p24f); }
@@ -302,6 +315,13 @@ template <int Q> struct Pops<Q, 1> {
     } else {
       return round(v);
     }
+  }
+  // the value a half store keeps of a b + c, rounded once (stochastically: the
+  // FP32 value is what is rounded)
+  template <bool SR>
+  __device__ __forceinline__ float fma_at(float a, float b, float c, uint32_t &rs) const {
+    if constexpr (SR) return round_at<SR>(__builtin_fmaf(a, b, c), rs);
+    else return half_fma(a, b, c);
   }
   __device__ __forceinline__ uint32_t step_key() const { return ctr ? ctr[0] : 0u; }
   __device__ __forceinline__ float ldf(int i, long long c) const { return __half2float(ld_at(f, blk_offset<2>(Q, i, c))); }
