@@ -242,17 +242,32 @@ template <class V> struct DirBits {
 template <class V> __host__ __device__ constexpr int cn(int i) { return V::D == 3 ? V::cz(i) : V::cy(i); }
 __device__ __forceinline__ int wall_layer(const Geom &G, int D) { return (D == 3 ? G.ez : G.ey) - 2; }
 
+// Solid cells of the lattices a kernel is compiled for.  What a kernel does about
+// walls is the same in every wave, but deciding it at run time costs registers,
+// spills and branches, also where there is nothing to decide.  Steps with
+// Geom's flags read in the kernels and now: four rollers in 512x512 cells (D2Q9)
+// 28.7 and 27.9 us, 64x64x32 between walls on every axis 55.1 and 52.8, 64x64x64
+// between flat walls 35.6 and 33.6 (FP16 26.4 and 24.5).
+enum Walls : int {
+  W_ANY = -1,    // read Geom's flags: batches, whose classes mix lattices, and reads
+  W_SOLIDS = 0,  // masks, rollers, walls on other axes
+  W_NONE = 1,    // no solid cell (Geom::plain)
+  W_FLAT = 2     // flat walls on the last axis (Geom::plain and flat)
+};
+template <int W> __device__ __forceinline__ bool is_plain(const Geom &G) { return W == W_ANY ? G.plain : W != W_SOLIDS; }
+template <int W> __device__ __forceinline__ bool is_flat(const Geom &G) { return W == W_ANY ? G.flat : W == W_FLAT; }
+
 // Neighbour word of a cell.  A plain lattice's follows from the cell's place
 // between the walls, the same for a whole wave and without a load before the
 // wave can start.  Else, in a 64-cell row segment flagged all-fluid (every
 // cell fluid, every neighbour fluid), it is 0 without reading nbm: each wave
 // of the single-lattice cell kernels covers exactly one segment, so the flag
 // is one scalar load per wave in place of 256 bytes of neighbour words.
-template <class V>
+template <class V, int W>
 __device__ __forceinline__ uint32_t nb_word(const Geom &G, const uint32_t *nbm, const uint8_t *segf, int y, int z,
                                             long long c) {
-  if (G.plain) {
-    if (!G.flat) return 0u;
+  if (is_plain<W>(G)) {
+    if (!is_flat<W>(G)) return 0u;
     const int n = V::D == 3 ? z : y, top = wall_layer(G, V::D);
     constexpr int ax = V::D == 3 ? 2 : 1;
     constexpr uint32_t low = DirBits<V>::with(ax, -1), high = DirBits<V>::with(ax, 1);
@@ -265,9 +280,9 @@ __device__ __forceinline__ uint32_t nb_word(const Geom &G, const uint32_t *nbm, 
   }
   return nbm[c];
 }
-template <int Q, int S>
+template <int Q, int S, int W>
 __device__ __forceinline__ uint32_t nb_word(const LatView<Q, S> &L, int y, int z, long long c) {
-  return nb_word<VSet<Q>>(L.G, L.nbm, L.segf, y, z, c);
+  return nb_word<VSet<Q>, W>(L.G, L.nbm, L.segf, y, z, c);
 }
 
 // Second pass for fluid cell c: adds the unavailable sources of each group,
@@ -320,11 +335,11 @@ __device__ __forceinline__ void second_pass(const LatView<Q, S> &L, const Nbr &N
 }
 
 // M from the populations alone (state parity ODD).
-template <int Q, int S, int ODD>
+template <int Q, int S, int ODD, int W>
 __device__ __forceinline__ void stage_moments(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
+  const uint32_t bits = nb_word<Q, S, W>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float df[Q], g[Q];
@@ -360,10 +375,10 @@ __device__ __forceinline__ void stage_moments(const LatView<Q, S> &L, int x, int
 }
 
 // Second pass after collide; the state at t+1 has parity PAR.
-template <int Q, int S, int PAR>
+template <int Q, int S, int PAR, int W>
 __device__ __forceinline__ void stage_combine(const LatView<Q, S> &L, int x, int y, int z) {
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
+  const uint32_t bits = nb_word<Q, S, W>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float2 grp[3];
@@ -428,9 +443,9 @@ __device__ __forceinline__ void fluid_mean(const float *__restrict__ X, uint32_t
 template <class V> __host__ __device__ constexpr int ct1(int i) { return V::D == 3 ? V::cy(i) : 0; }
 
 // whether a cell (on the last axis at n) has ghost neighbours of a flat wall
-template <class V> __device__ __forceinline__ bool by_flat_wall(const Geom &G, int y, int z) {
+template <class V, int W> __device__ __forceinline__ bool by_flat_wall(const Geom &G, int y, int z) {
   const int n = V::D == 3 ? z : y;
-  return G.flat && (n == 1 || n == wall_layer(G, V::D));
+  return is_flat<W>(G) && (n == 1 || n == wall_layer(G, V::D));
 }
 
 // Fill of the ghost cell of the wall at the low (SIDE = -1) or high (SIDE = 1)
@@ -606,11 +621,11 @@ __device__ __forceinline__ void force_of(Fetch fetch, float mu_rho, float mu_phi
 #pragma unroll
   for (int a = 0; a < 3; ++a) F[a] = mu_rho * gr[a] + mu_phi * gp[a] - gq[a];
 }
-template <int Q>
+template <int Q, int W>
 __device__ __forceinline__ void force(const float4 *__restrict__ C, const Geom &G, const Nbr &N, int x, int y, int z,
                                       float mu_rho, float mu_phi, float F[3]) {
   using V = VSet<Q>;
-  if (by_flat_wall<V>(G, y, z)) {  // the same for a whole wave
+  if (by_flat_wall<V, W>(G, y, z)) {  // the same for a whole wave
     float v[Q][3];
     wall_neighbours<Q, 3>(C, G, N, x, y, z, v);
     force_of<Q>([&](int i) { return make_float3(v[i][0], v[i][1], v[i][2]); }, mu_rho, mu_phi, F);
@@ -833,12 +848,12 @@ __device__ __forceinline__ void bounce_flat_side(const Pops<Q, S> &P, const Nbr 
 }
 
 // Bounce-back on the links in `bits`, by whichever of the two applies.
-template <int Q, int S, int ODD, bool WITH_G, bool SR, class GetF, class GetG>
+template <int Q, int S, int ODD, int W, bool WITH_G, bool SR, class GetF, class GetG>
 __device__ __forceinline__ void bounce_with(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x,
                                             int y, int z, float rho, float phi, uint32_t &rs, GetF get_f, GetG get_g) {
   using V = VSet<Q>;
   const int n = V::D == 3 ? z : y, top = wall_layer(L.G, V::D);
-  if (L.G.plain && top > 1) {
+  if (is_plain<W>(L.G) && top > 1) {
     if (n == 1) bounce_flat_side<Q, S, ODD, -1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
     else bounce_flat_side<Q, S, ODD, 1, WITH_G, SR>(L.P, N, c, L.ph, rho, phi, rs, get_f, get_g);
   } else {  // masks, rollers, other walls, or both flat walls at once
@@ -846,31 +861,33 @@ __device__ __forceinline__ void bounce_with(const LatView<Q, S> &L, const Nbr &N
   }
 }
 // The stored populations read back from where the collide put them.
-template <int Q, int S, int ODD, bool WITH_G = true, bool SR = false>
+template <int Q, int S, int ODD, int W, bool WITH_G = true, bool SR = false>
 __device__ __forceinline__ void bounce(const LatView<Q, S> &L, const Nbr &N, long long c, uint32_t bits, int x, int y,
                                        int z, float rho, float phi, uint32_t &rs) {
   using V = VSet<Q>;
   auto at = [&](int i) { return ODD ? (long long)N.template at<V>(i) : c; };
-  bounce_with<Q, S, ODD, WITH_G, SR>(
+  bounce_with<Q, S, ODD, W, WITH_G, SR>(
       L, N, c, bits, x, y, z, rho, phi, rs, [&](int i) { return L.P.ldfc(ODD ? i : opp(i), at(i)); },
       [&](int i) { return L.P.ldgc(ODD ? i : opp(i), at(i)); });
 }
 
-// Force and mu_phi of a cell from the coupling field, and its populations.
-// D2Q9 loads the populations before the force (one round of latency for
-// both).  D3Q19 loads them after it: with both in flight it holds 166
-// registers, one after the other 127 to 146 (256x128x128, even parity: FP32
-// 277 -> 258 us, FP16 159 -> 148; odd parity unchanged).
-template <int Q, int S, int ODD>
+// Force and mu_phi of a cell from the coupling field, then its populations.  With
+// both in flight the D3Q19 collide holds 166 registers, one after the other 96
+// to 126 on plain lattices (256x128x128, even parity: FP32 277 -> 258 us, FP16
+// 159 -> 148; odd parity unchanged), so there the order is held: without, the
+// compiler brings the loads forward again (a periodic 256x128x128 step: FP32
+// 355 instead of 348 us, FP16 237.7 instead of 235.2).  With masks it has no
+// effect.  D2Q9 with masks is level up to 512x512 cells whichever comes first,
+// from 1024x1024 on 1% faster this way.
+template <int Q, int S, int ODD, int W>
 __device__ __forceinline__ auto couple_and_load(const LatView<Q, S> &L, const Nbr &N, int x, int y, int z, long long c,
                                                 float *df, float *g) {
-  constexpr bool EARLY = Q == 9;
   return [=, &L, &N](float F[3], float &mu_phi) {
-    if constexpr (EARLY) load_collide<Q, S, ODD>(L.P, N, c, df, g);
     const float4 cc = L.C[c];
     mu_phi = cc.w;
-    force<Q>(L.C, L.G, N, x, y, z, coupling_mu_rho(cc), mu_phi, F);
-    if constexpr (!EARLY) load_collide<Q, S, ODD>(L.P, N, c, df, g);
+    force<Q, W>(L.C, L.G, N, x, y, z, coupling_mu_rho(cc), mu_phi, F);
+    if constexpr (W == W_NONE || W == W_FLAT) __builtin_amdgcn_sched_barrier(0);
+    load_collide<Q, S, ODD>(L.P, N, c, df, g);
   };
 }
 
@@ -922,22 +939,22 @@ __device__ __forceinline__ void moment_sums(const LatView<Q, S> &L, int x, int y
 // Collide and stream a cell.  With the by-product (FP32), every thread of
 // the 64 x COLLIDE_ROWS block must call this (it holds a barrier); `active`
 // marks threads on a storage cell.
-template <int Q, int S, int ODD, bool SR = false>
+template <int Q, int S, int ODD, int W, bool SR = false>
 __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int y, int z, bool active) {
   constexpr int NT = BX * COLLIDE_ROWS;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
   if (!ByProduct<S>::on) {
     if (!active) return;
-    const uint32_t bits = nb_word<Q, S>(L, y, z, c);
+    const uint32_t bits = nb_word<Q, S, W>(L, y, z, c);
     if (bits & NB_SELF_SOLID) return;
     const Nbr N(L.G, x, y, z);
     float rho, phi;
     float2 rest;
     uint32_t rs = SR ? sr_seed(c, L.P.step_key()) : 0u;
     float df[Q], g[Q];
-    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, nullptr,
+    collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple_and_load<Q, S, ODD, W>(L, N, x, y, z, c, df, g), df, g, L.ph, nullptr,
                                     0, rho, phi, rest, rs);
-    if (bits != 0u) bounce<Q, S, ODD, true, SR>(L, N, c, bits, x, y, z, rho, phi, rs);
+    if (bits != 0u) bounce<Q, S, ODD, W, true, SR>(L, N, c, bits, x, y, z, rho, phi, rs);
     return;
   }
   __shared__ float post[2 * (Q - 1)][NT];
@@ -946,17 +963,17 @@ __device__ __forceinline__ void stage_collide(const LatView<Q, S> &L, int x, int
   bool fluid = false;
   float2 rest = make_float2(0.0f, 0.0f);
   if (active) {
-    const uint32_t bits = nb_word<Q, S>(L, y, z, c);
+    const uint32_t bits = nb_word<Q, S, W>(L, y, z, c);
     fluid = !(bits & NB_SELF_SOLID);
     if (fluid) {
       const Nbr N(L.G, x, y, z);
       float rho, phi;
       uint32_t rs = 0u;
       float df[Q], g[Q];
-      collide_cell<Q, S, ODD, NT>(L.P, N, c, couple_and_load<Q, S, ODD>(L, N, x, y, z, c, df, g), df, g, L.ph, post,
+      collide_cell<Q, S, ODD, NT>(L.P, N, c, couple_and_load<Q, S, ODD, W>(L, N, x, y, z, c, df, g), df, g, L.ph, post,
                                   tid, rho, phi, rest, rs);
       if (bits != 0u)
-        bounce_with<Q, S, ODD, true, false>(L, N, c, bits, x, y, z, rho, phi, rs,
+        bounce_with<Q, S, ODD, W, true, false>(L, N, c, bits, x, y, z, rho, phi, rs,
                                             [&](int i) { return post[i - 1][tid]; },
                                             [&](int i) { return post[Q - 1 + i - 1][tid]; });
     }
@@ -984,11 +1001,11 @@ enum Stage {
 // rho = sum f evolves; g is not stepped.  The potential and force stages of
 // the step are reused on M = (rho - 1, phi0).
 // ---------------------------------------------------------------------------
-template <int Q, int S, int ODD>
+template <int Q, int S, int ODD, int W>
 __device__ __forceinline__ void stage_pre_moments(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  if (nb_word<Q, S>(L, y, z, c) & NB_SELF_SOLID) return;
+  if (nb_word<Q, S, W>(L, y, z, c) & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   float drho = 0.0f;
 #pragma unroll
@@ -996,17 +1013,17 @@ __device__ __forceinline__ void stage_pre_moments(const LatView<Q, S> &L, int x,
   L.M[c] = make_float2(drho, L.AUX[c].w);
 }
 
-template <int Q, int S, int ODD>
+template <int Q, int S, int ODD, int W>
 __device__ __forceinline__ void stage_pre_collide(const LatView<Q, S> &L, int x, int y, int z) {
   using V = VSet<Q>;
   const long long c = (long long)x + (long long)L.G.px * ((long long)y + (long long)L.G.ey * z);
-  const uint32_t bits = nb_word<Q, S>(L, y, z, c);
+  const uint32_t bits = nb_word<Q, S, W>(L, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(L.G, x, y, z);
   const float4 cc = L.C[c];
   const float mu_phi = cc.w, mu_rho = coupling_mu_rho(cc);
   float F[3];
-  force<Q>(L.C, L.G, N, x, y, z, mu_rho, mu_phi, F);
+  force<Q, W>(L.C, L.G, N, x, y, z, mu_rho, mu_phi, F);
   float df[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) df[i] = (!ODD || i == 0) ? L.P.ldf(i, c) : L.P.ldf(opp(i), N.template back<V>(i));
@@ -1031,28 +1048,28 @@ __device__ __forceinline__ void stage_pre_collide(const LatView<Q, S> &L, int x,
     else L.P.stf(i, N.template at<V>(i), fs);
   }
   uint32_t rs = 0u;
-  if (bits != 0u) bounce<Q, S, ODD, false>(L, N, c, bits, x, y, z, rho, 0.0f, rs);
+  if (bits != 0u) bounce<Q, S, ODD, W, false>(L, N, c, bits, x, y, z, rho, 0.0f, rs);
 }
 
 // Per-cell stages other than collide (ODD: parity of the state they read).
-template <int Q, int S, int STAGE, int ODD>
+template <int Q, int S, int STAGE, int ODD, int W>
 __device__ __forceinline__ void run_stage(const LatView<Q, S> &L, int x, int y, int z) {
-  if constexpr (STAGE == ST_MOMENTS) stage_moments<Q, S, ODD>(L, x, y, z);
-  else if constexpr (STAGE == ST_COMBINE) stage_combine<Q, S, ODD>(L, x, y, z);
-  else if constexpr (STAGE == ST_PRE_MOMENTS) stage_pre_moments<Q, S, ODD>(L, x, y, z);
-  else stage_pre_collide<Q, S, ODD>(L, x, y, z);
+  if constexpr (STAGE == ST_MOMENTS) stage_moments<Q, S, ODD, W>(L, x, y, z);
+  else if constexpr (STAGE == ST_COMBINE) stage_combine<Q, S, ODD, W>(L, x, y, z);
+  else if constexpr (STAGE == ST_PRE_MOMENTS) stage_pre_moments<Q, S, ODD, W>(L, x, y, z);
+  else stage_pre_collide<Q, S, ODD, W>(L, x, y, z);
 }
 
 // The collide keeps the compiler's register choice (3 waves per SIMD for
 // D3Q19): capped at 128 VGPRs (4 waves) it spills 52-56 bytes per lane in FP16
 // storage and was measured 16% slower (186 against 160 us at 256x128x128).
-template <int Q, int S, int STAGE, int ODD, bool SR = false>
+template <int Q, int S, int STAGE, int ODD, int W, bool SR = false>
 __global__ __launch_bounds__(BX *MAX_ROWS) void k_cells(LatView<Q, S> L) {
   int x, y, z;
   long long c;
   const bool in = cell_of_tile(L.G, L.tm, x, y, z, c);
   if (STAGE == ST_COLLIDE) {
-    stage_collide<Q, S, ODD, SR>(L, x, y, z, in);
+    stage_collide<Q, S, ODD, W, SR>(L, x, y, z, in);
     return;
   }
   if constexpr (S == 1 && STAGE == ST_MOMENTS) {
@@ -1060,7 +1077,7 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_cells(LatView<Q, S> L) {
     // collide: the counter the collide reads advances once per step
     if (L.tick && L.P.ctr && blockIdx.x == 0 && threadIdx.x == 0 && threadIdx.y == 0) L.P.ctr[0] += 1u;
   }
-  if (in) run_stage<Q, S, STAGE, ODD>(L, x, y, z);
+  if (in) run_stage<Q, S, STAGE, ODD, W>(L, x, y, z);
 }
 
 template <int Q, int S, int PI>
@@ -1082,7 +1099,7 @@ using PotRing = float2[3][MAX_ROWS + 2][RING_W];
 // The potential of planes [z0, z1) of the 64 x blockDim.y column (bx, by);
 // every thread of the block takes part (barriers), and the ring is free
 // again on return.
-template <int Q, int S>
+template <int Q, int S, int W>
 __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing &ring, int bx, int by, int z0,
                                                  int z1) {
   using V = VSet<Q>;
@@ -1100,7 +1117,7 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
     int zz = zs;
     if (zz < 0 || zz >= G.ez) zz = G.per[2] ? wrap(zz, G.ez) : -1;
     const int top = wall_layer(G, V::D);
-    const bool ghosts = V::D == 3 && G.flat && (zz == 0 || zz == top + 1);  // a whole plane of them
+    const bool ghosts = V::D == 3 && is_flat<W>(G) && (zz == 0 || zz == top + 1);  // a whole plane of them
     for (int k = tid; k < hcells; k += nth) {
       const int hy = k / HW, hx = k - hy * HW;
       float2 v = make_float2(0.0f, 0.0f);
@@ -1110,7 +1127,7 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
         if (xg < 0 || xg >= G.ex) { if (G.per[0]) xg = wrap(xg, G.ex); else ok = false; }
         if (yg < 0 || yg >= G.ey) { if (G.per[1]) yg = wrap(yg, G.ey); else ok = false; }
         if (ok) {
-          if (ghosts || (V::D == 2 && G.flat && (yg == 0 || yg == top + 1))) v = ghost_moments<Q>(L.M, G, xg, yg, zz);
+          if (ghosts || (V::D == 2 && is_flat<W>(G) && (yg == 0 || yg == top + 1))) v = ghost_moments<Q>(L.M, G, xg, yg, zz);
           else v = L.M[(long long)xg + (long long)G.px * ((long long)yg + (long long)G.ey * zz)];
         }
       }
@@ -1126,7 +1143,7 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
     __syncthreads();
     if (tx < w && ty < h) {
       const long long c = (long long)(xlo + tx) + (long long)G.px * ((long long)(ylo + ty) + (long long)G.ey * z);
-      if (!(nb_word<Q, S>(L, ylo + ty, z, c) & NB_SELF_SOLID)) {
+      if (!(nb_word<Q, S, W>(L, ylo + ty, z, c) & NB_SELF_SOLID)) {
         const float2 m0 = ring[sc][ty + 1][tx + 1];
         float lr, lp;
         laplacians<Q>([&](int i) {
@@ -1140,23 +1157,14 @@ __device__ __forceinline__ void potential_column(const LatView<Q, S> &L, PotRing
   }
 }
 
-// Scalar registers of the z-marching potentials.  A wave is given them in
-// sixteens with 16 more for the trap handler, 800 a SIMD: above 80 a CU holds 7
-// of the 4-row blocks, not 8, and a grid of 8 per CU takes a second, nearly empty
-// turn (88 registers: 310 us at 512x256x256 and 46 in the four-roller cell,
-// against 247 and 38 with 76; capped, a step at 512x256x256 takes 2855 instead
-// of 2897 us FP32 and 2042 instead of 2095 FP16).  What the cap moves to vector
-// registers costs 0.3 us on small lattices.
-constexpr int POT_SGPRS = 80;
-
-template <int Q, int S>
-__global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SGPRS))) void k_potential_zm(LatView<Q, S> L, int tz) {
+template <int Q, int S, int W>
+__global__ __launch_bounds__(BX *MAX_ROWS) void k_potential_zm(LatView<Q, S> L, int tz) {
   __shared__ PotRing ring;
   uint32_t ubx, ur;
   tile_of_block(L.tm, blockIdx.x, ubx, ur);
   const uint32_t uch = udiv(ur, L.tm.dgy);
   const int by = (int)(ur - uch * (uint32_t)L.tm.gy), z0 = (int)uch * tz;
-  potential_column<Q, S>(L, ring, (int)ubx, by, z0, min(z0 + tz, L.G.ez));
+  potential_column<Q, S, W>(L, ring, (int)ubx, by, z0, min(z0 + tz, L.G.ez));
 }
 
 // ---------------------------------------------------------------------------
@@ -1187,7 +1195,7 @@ __device__ __forceinline__ int wrap_far(int v, int n) {
 
 template <int S, int ODD, bool SR = false>
 __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L) {
-  constexpr int Q = 9, R = COLLIDE_ROWS, NT = BX * R;
+  constexpr int Q = 9, R = COLLIDE_ROWS, NT = BX * R, W = W_ANY;
   using V = VSet<Q>;
   constexpr bool BP = ByProduct<S>::on;
   constexpr int HX = 3, HY = 2, PX = 2, PY = 1;  // reach of the moments and of Pi
@@ -1268,7 +1276,7 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
         const float2 m = mom[ty + HY + V::cy(i)][tx + HX + V::cx(i)];
         return make_float3(m.x, m.y, pis[ty + PY + V::cy(i)][tx + PX + V::cx(i)]);
       };
-      if (by_flat_wall<V>(G, y, 0)) {
+      if (by_flat_wall<V, W>(G, y, 0)) {
         // Pi of the three ghost cells, from the cell's own row
         float low[3], high[3];
 #pragma unroll
@@ -1290,9 +1298,9 @@ __global__ __launch_bounds__(BX *COLLIDE_ROWS) void k_collide_2d(LatView<9, S> L
     float(*tile)[NT] = nullptr;
     if constexpr (BP) tile = post;
     collide_cell<Q, S, ODD, NT, SR>(L.P, N, c, couple, df, g, L.ph, tile, tid, rho, phi, rest, rs);
-    const uint32_t bits = nb_word<Q, S>(L, y, 0, c);
+    const uint32_t bits = nb_word<Q, S, W>(L, y, 0, c);
     if (bits != 0u)
-      bounce_with<Q, S, ODD, true, SR>(L, N, c, bits, x, y, 0, rho, phi, rs, [&](int i) { return df[i]; },
+      bounce_with<Q, S, ODD, W, true, SR>(L, N, c, bits, x, y, 0, rho, phi, rs, [&](int i) { return df[i]; },
                                        [&](int i) { return g[i]; });
   }
   if constexpr (BP) {
@@ -1335,13 +1343,20 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_cells(char *base, const 
     const int y = __builtin_amdgcn_readfirstlane(it.z * (int)blockDim.y + (int)threadIdx.y);
     const bool in = x < L.G.ex && y < L.G.ey;
     if (STAGE == ST_COLLIDE) {
-      stage_collide<Q, S, ODD>(L, x, y, z, in);
+      stage_collide<Q, S, ODD, W_ANY>(L, x, y, z, in);
       if (ByProduct<S>::on) __syncthreads();  // the tile buffer is reused by the next item
     } else if (in) {
-      run_stage<Q, S, STAGE, ODD>(L, x, y, z);
+      run_stage<Q, S, STAGE, ODD, W_ANY>(L, x, y, z);
     }
   }
 }
+
+// Scalar registers of the batch potential.  A wave is given them in sixteens
+// with 16 more for the trap handler, 800 a SIMD: above 80 a CU holds 7 of the
+// 4-row blocks, not 8, and the grid of 8 per CU takes a second, nearly empty
+// turn (the mixed batch of 8: 254.7 us a step, capped 253).  k_potential_zm,
+// compiled for one kind of walls, takes 62 to 76.
+constexpr int POT_SGPRS = 80;
 
 // The batch potential: z-marching columns (slot, block-x, block-y, first
 // plane) of range[2] planes each, as k_potential_zm marches them.
@@ -1354,7 +1369,7 @@ __global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SG
   for (int w = blockIdx.x; w < n; w += gridDim.x) {
     const int4 it = cols[start + w];
     const LatView<Q, S> L = view_of<Q, S>(base, inst[it.x]);
-    potential_column<Q, S>(L, ring, it.y, it.z, it.w, min(it.w + tz, L.G.ez));
+    potential_column<Q, S, W_ANY>(L, ring, it.y, it.z, it.w, min(it.w + tz, L.G.ez));
   }
 }
 
@@ -1459,7 +1474,7 @@ __global__ __launch_bounds__(BX *BY) void k_observe(Pops<Q, S> P, const uint32_t
   }
   const float4 m0 = C[c];
   float F[3];
-  force<Q>(C, G, N, x, y, z, coupling_mu_rho(m0), m0.w, F);
+  force<Q, W_ANY>(C, G, N, x, y, z, coupling_mu_rho(m0), m0.w, F);
   const float rho = 1.0f + m0.x;
   const float inv = 1.0f / rho;
   // P = cs^2 rho + rho mu_rho + phi mu_phi - psi_b, with Pi = rho mu_rho + phi mu_phi
@@ -1658,13 +1673,13 @@ __device__ __forceinline__ float ld3(const T3View<Q> &T, const float *a, const N
 
 // The moments from the populations alone: the additions of k3_collide and
 // k3_combine in their order (per group the available sources, then the others).
-template <int Q>
+template <int Q, int W>
 __global__ __launch_bounds__(BX *BY) void k3_moments(T3View<Q> T, int odd) {
   using V = VSet<Q>;
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  const uint32_t bits = nb_word<V>(T.G, T.nbm, nullptr, y, z, c);
+  const uint32_t bits = nb_word<V, W>(T.G, T.nbm, nullptr, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   const float *pop[3] = {T.f, T.g, T.h};
@@ -1718,14 +1733,14 @@ __device__ __forceinline__ void t3_sums(const T3View<Q> &T, int p, int x, int y,
 
 // Second pass after the collide (as second_pass); the state at t+1 has parity
 // `par`.
-template <int Q>
+template <int Q, int W>
 __global__ __launch_bounds__(BX *BY) void k3_combine(T3View<Q> T, int par) {
   using V = VSet<Q>;
   using B = DirBits<V>;
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
-  const uint32_t bits = nb_word<V>(T.G, T.nbm, nullptr, y, z, c);
+  const uint32_t bits = nb_word<V, W>(T.G, T.nbm, nullptr, y, z, c);
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   float grp[3][3];
@@ -1791,7 +1806,7 @@ __global__ __launch_bounds__(256) void k3_fill(T3View<Q> T) {
 }
 
 // INIT: the fill kernel has stored every ghost cell's M
-template <int Q, bool INIT>
+template <int Q, bool INIT, int W>
 __device__ __forceinline__ void t3_potential_at(const T3View<Q> &T, const Nbr &N, int x, int y, int z, long long c) {
   using V = VSet<Q>;
   const float4 m0 = T.M4[c];
@@ -1801,7 +1816,7 @@ __device__ __forceinline__ void t3_potential_at(const T3View<Q> &T, const Nbr &N
     ap += V::w(i) * (my - m0.y);
     aq += V::w(i) * (mz - m0.z);
   };
-  if (!INIT && by_flat_wall<V>(T.G, y, z)) {
+  if (!INIT && by_flat_wall<V, W>(T.G, y, z)) {
     float v[Q][3];
     wall_neighbours<Q, 3>(T.M4, T.G, N, x, y, z, v);
 #pragma unroll
@@ -1819,17 +1834,17 @@ __device__ __forceinline__ void t3_potential_at(const T3View<Q> &T, const Nbr &N
   T.CM[c] = make_float2(mp, mq);
 }
 
-template <int Q>
+template <int Q, int W>
 __global__ __launch_bounds__(BX *BY) void k3_potential(T3View<Q> T) {
   int x, y, z;
   long long c;
   if (!cell_of_thread(T.G, x, y, z, c)) return;
-  if (nb_word<VSet<Q>>(T.G, T.nbm, nullptr, y, z, c) & NB_SELF_SOLID) return;
-  t3_potential_at<Q, false>(T, Nbr(T.G, x, y, z), x, y, z, c);
+  if (nb_word<VSet<Q>, W>(T.G, T.nbm, nullptr, y, z, c) & NB_SELF_SOLID) return;
+  t3_potential_at<Q, false, W>(T, Nbr(T.G, x, y, z), x, y, z, c);
 }
 
 // force and mu_rho of a fluid cell from C4, CM
-template <int Q>
+template <int Q, int W>
 __device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, int x, int y, int z, long long c,
                                          float F[3], float &mu_phi, float &mu_psi) {
   using V = VSet<Q>;
@@ -1851,7 +1866,7 @@ __device__ __forceinline__ void t3_force(const T3View<Q> &T, const Nbr &N, int x
       gw[a] += cv[a] * w * mw;
     }
   };
-  if (by_flat_wall<V>(T.G, y, z)) {
+  if (by_flat_wall<V, W>(T.G, y, z)) {
     float v[Q][4];
     wall_neighbours<Q, 4>(T.C4, T.G, N, x, y, z, v);
 #pragma unroll
@@ -1906,7 +1921,7 @@ __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __h
 // each in 3D): the share of one population in the moments at t+1 is summed
 // while the next is collided into the other buffer, and a population is loaded
 // while the one before it is collided.
-template <int Q, int ODD>
+template <int Q, int ODD, int W>
 __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   using V = VSet<Q>;
   constexpr int NT = BX * BY;
@@ -1917,7 +1932,7 @@ __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   long long c = 0;
   const bool in = cell_of_tile(T.G, T.tm, x, y, z, c);
   const int tid = threadIdx.y * BX + threadIdx.x;
-  const uint32_t bits = in ? nb_word<V>(T.G, T.nbm, nullptr, y, z, c) : NB_SELF_SOLID;
+  const uint32_t bits = in ? nb_word<V, W>(T.G, T.nbm, nullptr, y, z, c) : NB_SELF_SOLID;
   const bool fluid = !(bits & NB_SELF_SOLID);
   const Nbr N(T.G, x, y, z);
   float m[3], inv_rho = 0.0f, mmr = 0.0f, mu_phi = 0.0f, mu_psi = 0.0f;
@@ -1925,7 +1940,7 @@ __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   live[tid] = fluid ? 1 : 0;
   if (fluid) {
     float F[3];
-    t3_force<Q>(T, N, x, y, z, c, F, mu_phi, mu_psi);
+    t3_force<Q, W>(T, N, x, y, z, c, F, mu_phi, mu_psi);
     // f: BGK with the Guo term, first moments exact as in collide_cell
     float df[Q];
 #pragma unroll
@@ -2007,7 +2022,7 @@ __global__ __launch_bounds__(BX *BY) void k3_init(T3View<Q> T) {
   if (!cell_of_thread(T.G, x, y, z, c)) return;
   if (T.nbm[c] & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
-  t3_potential_at<Q, true>(T, N, x, y, z, c);
+  t3_potential_at<Q, true, W_ANY>(T, N, x, y, z, c);
   const float4 m0 = T.M4[c];
   const float2 mu = T.CM[c];
   const float4 u4 = T.AUX[c];
@@ -2046,7 +2061,7 @@ __global__ __launch_bounds__(BX *BY) void k3_observe(T3View<Q> T, int odd) {
   }
   const Nbr N(T.G, x, y, z);
   float F[3], mp, mq;
-  t3_force<Q>(T, N, x, y, z, c, F, mp, mq);
+  t3_force<Q, W_ANY>(T, N, x, y, z, c, F, mp, mq);
   float j[3] = {0, 0, 0};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -2118,6 +2133,17 @@ static LatView<Q, S> view_of_args(const LaunchArgs &a) {
   return L;
 }
 
+// f with the Walls of the lattice as a constant (PLAIN: whether a plain lattice
+// comes here).
+template <bool PLAIN = true, class F>
+static void for_walls(const LaunchArgs &a, F f) {
+  if constexpr (PLAIN) {
+    if (a.G.flat) return f(std::integral_constant<int, W_FLAT>{});
+    if (a.G.plain) return f(std::integral_constant<int, W_NONE>{});
+  }
+  f(std::integral_constant<int, W_SOLIDS>{});
+}
+
 // Launch of a cell stage with its shape (the moments pass -- k_moments or
 // k_combine -- uses shape 0; with the by-product the collide tile always has
 // COLLIDE_ROWS rows and only its block order varies).
@@ -2130,15 +2156,30 @@ static void cells_launch(const LaunchArgs &a, int odd, int tick = 0) {
   const dim3 grid = tile_grid(a.G, rows), block(BX, rows, 1);
   L.tm = TileMap(a.G.ex, a.G.ey, rows, (int)grid.x, sh.xcd);
   if (S == 0 && (STAGE == ST_COLLIDE || STAGE == ST_COMBINE)) alternate(L.tm, odd);
-  if constexpr (S == 1 && STAGE == ST_COLLIDE) {
-    if (a.ctr) {  // stochastic rounding
-      if (odd) k_cells<Q, S, STAGE, 1, true><<<grid, block, 0, a.stream>>>(L);
-      else k_cells<Q, S, STAGE, 0, true><<<grid, block, 0, a.stream>>>(L);
-      return;
+  auto go = [&](auto walls) {
+    constexpr int W = decltype(walls)::value;
+    if constexpr (S == 1 && STAGE == ST_COLLIDE) {
+      if (a.ctr) {  // stochastic rounding
+        if (odd) k_cells<Q, S, STAGE, 1, W, true><<<grid, block, 0, a.stream>>>(L);
+        else k_cells<Q, S, STAGE, 0, W, true><<<grid, block, 0, a.stream>>>(L);
+        return;
+      }
     }
+    if (odd) k_cells<Q, S, STAGE, 1, W><<<grid, block, 0, a.stream>>>(L);
+    else k_cells<Q, S, STAGE, 0, W><<<grid, block, 0, a.stream>>>(L);
+  };
+  if constexpr (Q == 19 && STAGE == ST_COLLIDE) {
+    // With masks the collide for them alone takes 139-166 registers (3 waves per
+    // SIMD), the one that reads Geom's flags 106-138.  The first is faster
+    // while the chip holds all waves at once (64x64x32 between walls on every
+    // axis 52.4 against 54.0 us a step, FP16 49.1 against 49.7), the second
+    // beyond (four rollers in 96x96x48: 80.4 against 81.4, FP16 74.5 against
+    // 76.7; in 256x256x64: 434.6 against 441.3, 320.5 against 332.4).
+    if (!a.G.plain && (long long)a.G.ex * a.G.ey * a.G.ez > 3 * 4 * 256 * 64)
+      return go(std::integral_constant<int, W_ANY>{});
   }
-  if (odd) k_cells<Q, S, STAGE, 1><<<grid, block, 0, a.stream>>>(L);
-  else k_cells<Q, S, STAGE, 0><<<grid, block, 0, a.stream>>>(L);
+  // plain D2Q9 lattices collide in k_collide_2d
+  for_walls<!(Q == 9 && STAGE == ST_COLLIDE)>(a, go);
 }
 
 // the fill of M runs at initialisation for every lattice (k_init reads it)
@@ -2162,7 +2203,9 @@ static void potential_launch(const LaunchArgs &a) {
   const int tz = (a.G.ez + nch - 1) / nch;
   nch = (a.G.ez + tz - 1) / tz;
   L.tm = TileMap(a.G.ex, a.G.ey, sh.rows, tiles * nch, sh.xcd);
-  k_potential_zm<Q, S><<<dim3((unsigned)(tiles * nch)), dim3(BX, sh.rows, 1), 0, a.stream>>>(L, tz);
+  for_walls(a, [&](auto walls) {
+    k_potential_zm<Q, S, decltype(walls)::value><<<dim3((unsigned)(tiles * nch)), dim3(BX, sh.rows, 1), 0, a.stream>>>(L, tz);
+  });
 }
 
 bool forms_potential(const LaunchArgs &a) { return a.q == 9 && a.G.plain && !a.ternary; }
@@ -2378,7 +2421,9 @@ static void t3_couple(const LaunchArgs &a) {
   const T3View<Q> T = t3_view<Q>(a);
   const bool fills = a.n_fill && !a.G.flat;
   if (fills) k3_fill<Q, 0><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
-  k3_potential<Q><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(T);
+  for_walls(a, [&](auto walls) {
+    k3_potential<Q, decltype(walls)::value><<<cell_grid(a.G), cell_block(), 0, a.stream>>>(T);
+  });
   if (fills) k3_fill<Q, 1><<<fill_blocks(a.n_fill), 256, 0, a.stream>>>(T);
 }
 
@@ -2387,10 +2432,13 @@ static void t3_step(const LaunchArgs &a, int odd) {
   t3_couple<Q>(a);
   T3View<Q> T = t3_view<Q>(a);
   const dim3 tiles = t3_tiles<Q>(a, T, odd);
-  if (odd) k3_collide<Q, 1><<<tiles, cell_block(), 0, a.stream>>>(T);
-  else k3_collide<Q, 0><<<tiles, cell_block(), 0, a.stream>>>(T);
-  t3_tiles<Q>(a, T, odd ^ 1);
-  k3_combine<Q><<<tiles, cell_block(), 0, a.stream>>>(T, odd ^ 1);
+  for_walls(a, [&](auto walls) {
+    constexpr int W = decltype(walls)::value;
+    if (odd) k3_collide<Q, 1, W><<<tiles, cell_block(), 0, a.stream>>>(T);
+    else k3_collide<Q, 0, W><<<tiles, cell_block(), 0, a.stream>>>(T);
+    t3_tiles<Q>(a, T, odd ^ 1);
+    k3_combine<Q, W><<<tiles, cell_block(), 0, a.stream>>>(T, odd ^ 1);
+  });
 }
 
 void launch_step3(const LaunchArgs &a, int odd) {
@@ -2398,16 +2446,17 @@ void launch_step3(const LaunchArgs &a, int odd) {
   else t3_step<19>(a, odd);
 }
 
+template <int Q>
+static void t3_moments(const LaunchArgs &a, int odd) {
+  T3View<Q> T = t3_view<Q>(a);
+  const dim3 tiles = t3_tiles<Q>(a, T, odd);
+  for_walls(a, [&](auto walls) {
+    k3_moments<Q, decltype(walls)::value><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
+  });
+}
 void launch_moments3(const LaunchArgs &a, int odd) {
-  if (a.q == 9) {
-    T3View<9> T = t3_view<9>(a);
-    const dim3 tiles = t3_tiles<9>(a, T, odd);
-    k3_moments<9><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
-  } else {
-    T3View<19> T = t3_view<19>(a);
-    const dim3 tiles = t3_tiles<19>(a, T, odd);
-    k3_moments<19><<<tiles, cell_block(), 0, a.stream>>>(T, odd);
-  }
+  if (a.q == 9) t3_moments<9>(a, odd);
+  else t3_moments<19>(a, odd);
 }
 
 void launch_observe3(const LaunchArgs &a, int odd) {
