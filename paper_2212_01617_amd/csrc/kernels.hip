@@ -1626,11 +1626,12 @@ __global__ __launch_bounds__(64) void k_reduce_final(const double *__restrict__ 
 // Ternary lattices (Sec. 2.2, Remark after the mobility relation): a third
 // order parameter psi with its own population h, FP32 storage, one thread
 // per cell in each pass.  A step is k3_fill (M), k3_potential, k3_fill (Pi),
-// k3_collide, k3_combine, the moments at t+1 being a by-product of the collide
-// as in the binary FP32 step (k3_moments runs after the populations are set
-// from outside).  At 256x128x128 a separate moments pass over the three
-// populations takes 203 us; the sums cost the collide 59 us (361 -> 420) and
-// k3_combine takes 87.  The arithmetic follows the binary stages, with
+// k3_collide and then, for the moments at t+1, k3_combine on large lattices, where
+// they are a by-product of the collide as in the binary FP32 step, and
+// k3_moments on small ones (t3_sums_moments; also after the populations are set
+// from outside).  At 256x128x128 the moments pass over the three populations
+// takes 203 us; the sums cost the collide 59 us (361 -> 420) and k3_combine
+// takes 87.  The arithmetic follows the binary stages, with
 // the potentials of chem_pot3 and the force
 //   mu_rho grad rho + mu_phi grad phi + mu_psi grad psi - grad Pi,
 //   Pi = rho mu_rho + phi mu_phi + psi mu_psi,
@@ -1671,6 +1672,19 @@ __device__ __forceinline__ float ld3(const T3View<Q> &T, const float *a, const N
   return (!odd || i == 0) ? T.template ld<NT>(a, i, c) : T.template ld<NT>(a, opp(i), N.template back<V>(i));
 }
 
+// Directions whose source is not available to the first pass of cell (x, y):
+// solid, or outside the collide's tile.  side: those that the tile's sides left.
+template <class V>
+__device__ __forceinline__ uint32_t unavailable(const Geom &G, int x, int y, uint32_t bits, uint32_t *side = nullptr) {
+  using B = DirBits<V>;
+  const int xlo = x & ~(BX - 1), ylo = (y / COLLIDE_ROWS) * COLLIDE_ROWS;
+  const uint32_t solid = B::solid_sources(bits);
+  const uint32_t xe = (x == xlo ? B::XP : 0u) | (x == min(xlo + BX, G.ex) - 1 ? B::XM : 0u);
+  const uint32_t ye = (y == ylo ? B::YP : 0u) | (y == min(ylo + COLLIDE_ROWS, G.ey) - 1 ? B::YM : 0u);
+  if (side) *side = xe & ~solid;
+  return solid | xe | ye;
+}
+
 // The moments from the populations alone: the additions of k3_collide and
 // k3_combine in their order (per group the available sources, then the others).
 template <int Q, int W>
@@ -1683,20 +1697,24 @@ __global__ __launch_bounds__(BX *BY) void k3_moments(T3View<Q> T, int odd) {
   if (bits & NB_SELF_SOLID) return;
   const Nbr N(T.G, x, y, z);
   const float *pop[3] = {T.f, T.g, T.h};
-  float m[3];
+  const uint32_t un = unavailable<V>(T.G, x, y, bits);
+  float v[3][Q], grp[3][3] = {}, m[3];
 #pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    float v[Q], grp[3] = {0.0f, 0.0f, 0.0f};
+  for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int i = 0; i < Q; ++i) v[i] = ld3<Q, true>(T, pop[p], N, c, odd, i);
+    for (int i = 0; i < Q; ++i) v[p][i] = ld3<Q, true>(T, pop[p], N, c, odd, i);
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
-      if (available<V>(T.G, x, y, bits, i)) grp[V::cz(i) + 1] += v[i];
+  for (int i = 0; i < Q; ++i)
 #pragma unroll
-    for (int i = 1; i < Q; ++i)
-      if (!available<V>(T.G, x, y, bits, i)) grp[V::cz(i) + 1] += v[i];
-    m[p] = V::D == 2 ? grp[1] : (grp[2] + grp[1]) + grp[0];
+    for (int p = 0; p < 3; ++p) grp[p][V::cz(i) + 1] += (un >> i) & 1u ? 0.0f : v[p][i];
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    if (!__any((un >> i) & 1u)) continue;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) grp[p][V::cz(i) + 1] += (un >> i) & 1u ? v[p][i] : 0.0f;
   }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) m[p] = V::D == 2 ? grp[p][1] : (grp[p][2] + grp[p][1]) + grp[p][0];
   T.M4[c] = make_float4(m[0], m[1], m[2], 0.0f);
 }
 
@@ -1736,7 +1754,6 @@ __device__ __forceinline__ void t3_sums(const T3View<Q> &T, int p, int x, int y,
 template <int Q, int W>
 __global__ __launch_bounds__(BX *BY) void k3_combine(T3View<Q> T, int par) {
   using V = VSet<Q>;
-  using B = DirBits<V>;
   int x, y, z;
   long long c;
   if (!cell_of_tile(T.G, T.tm, x, y, z, c)) return;
@@ -1748,11 +1765,8 @@ __global__ __launch_bounds__(BX *BY) void k3_combine(T3View<Q> T, int par) {
   for (int p = 0; p < 3; ++p)
 #pragma unroll
     for (int k = 0; k < 3; ++k) grp[p][k] = (V::D == 3 || k == 1) ? T.group(k, p)[c] : 0.0f;
-  const int xlo = x & ~(BX - 1), ylo = (y / COLLIDE_ROWS) * COLLIDE_ROWS;
-  const uint32_t solid = B::solid_sources(bits);
-  const uint32_t xe = (x == xlo ? B::XP : 0u) | (x == min(xlo + BX, T.G.ex) - 1 ? B::XM : 0u);
-  const uint32_t ye = (y == ylo ? B::YP : 0u) | (y == min(ylo + COLLIDE_ROWS, T.G.ey) - 1 ? B::YM : 0u);
-  const uint32_t un = solid | xe | ye, side = xe & ~solid;
+  uint32_t side;
+  const uint32_t un = unavailable<V>(T.G, x, y, bits, &side);
   const float *pop[3] = {T.f, T.g, T.h};
   float v[3][Q];
 #pragma unroll
@@ -1904,7 +1918,7 @@ __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __h
     const float eq = V::w(i) * gam3 * mu + X * (V::a(i) * cu + V::w(i) * ((4.5f * cmi * cu - 1.5f * mmr) * inv_rho));
     rest += eq;
     const float s = v[i] + om * (eq - v[i]);
-    post[i - 1][tid] = s;
+    if (post) post[i - 1][tid] = s;
     if (!ODD) T.st(a, opp(i), c, s);
     else T.st(a, i, N.template at<V>(i), s);
   }
@@ -1917,28 +1931,37 @@ __device__ __forceinline__ float t3_collide_ch(const T3View<Q> &T, float *a, __h
   return X;
 }
 
-// f, g and h in turn, through two LDS buffers of post-collision values (18 KB
-// each in 3D): the share of one population in the moments at t+1 is summed
-// while the next is collided into the other buffer, and a population is loaded
-// while the one before it is collided.
-template <int Q, int ODD, int W>
+// With SUMS f, g and h in turn, through two LDS buffers of post-collision values
+// (18 KB each in 3D): the share of one population in the moments at t+1 is
+// summed while the next is collided into the other buffer, and a population is
+// loaded while the one before it is collided.
+template <int Q, int ODD, int W, bool SUMS>
 __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
   using V = VSet<Q>;
   constexpr int NT = BX * BY;
   static_assert(BY == COLLIDE_ROWS, "the tile is the footprint of the sums");
-  __shared__ float post[2][Q - 1][NT];
-  __shared__ unsigned char live[NT];
+  __shared__ float lds[SUMS ? 2 : 1][SUMS ? Q - 1 : 1][SUMS ? NT : 1];
+  __shared__ unsigned char live[SUMS ? NT : 1];
+  float(*post[2])[NT] = {nullptr, nullptr};
+  if constexpr (SUMS) { post[0] = lds[0]; post[1] = lds[1]; }
   int x, y, z;
   long long c = 0;
   const bool in = cell_of_tile(T.G, T.tm, x, y, z, c);
   const int tid = threadIdx.y * BX + threadIdx.x;
   const uint32_t bits = in ? nb_word<V, W>(T.G, T.nbm, nullptr, y, z, c) : NB_SELF_SOLID;
   const bool fluid = !(bits & NB_SELF_SOLID);
+  // without SUMS one straight line, of which the compiler brings more loads
+  // forward; with masks that takes 164 registers instead of 120 (128x128x64 with
+  // rollers 222 instead of 198 us a step, 64x64x32 45.5 instead of 45.7)
+  constexpr bool STRAIGHT = !SUMS && (Q == 9 || W != W_SOLIDS);
+  if constexpr (STRAIGHT) {
+    if (!fluid) return;
+  }
   const Nbr N(T.G, x, y, z);
   float m[3], inv_rho = 0.0f, mmr = 0.0f, mu_phi = 0.0f, mu_psi = 0.0f;
   float rho = 0.0f, phi = 0.0f, psi = 0.0f, rest[3] = {0.0f, 0.0f, 0.0f}, v[Q], u[Q];
-  live[tid] = fluid ? 1 : 0;
-  if (fluid) {
+  if constexpr (SUMS) live[tid] = fluid ? 1 : 0;
+  if (STRAIGHT || fluid) {
     float F[3];
     t3_force<Q, W>(T, N, x, y, z, c, F, mu_phi, mu_psi);
     // f: BGK with the Guo term, first moments exact as in collide_cell
@@ -1972,26 +1995,30 @@ __global__ __launch_bounds__(BX *BY) void k3_collide(T3View<Q> T) {
       const float src = T.ph.guo * (ai * cF - 3.0f * wi * uF + 3.0f * ai * cu * cF);
       const float fs = df[i] + T.ph.om_f * (dfeq - df[i]) + src;
       if (i == 0) rest[0] = fs;
-      else post[0][i - 1][tid] = fs;
+      else if (SUMS) post[0][i - 1][tid] = fs;
       if (!ODD || i == 0) T.st(T.f, i == 0 ? 0 : opp(i), c, fs);
       else T.st(T.f, i, N.template at<V>(i), fs);
     }
   }
-  __syncthreads();
-  if (fluid) {
+  if constexpr (SUMS) __syncthreads();
+  if (STRAIGHT || fluid) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) u[i] = ld3<Q>(T, T.h, N, c, ODD, i);
-    phi = t3_collide_ch<Q, ODD>(T, T.g, T.g0l, N, c, m, inv_rho, mmr, mu_phi, T.ph.gam3, T.ph.om_g, v, post[1], tid,
-                                rest[1]);
+    phi = t3_collide_ch<Q, ODD, NT>(T, T.g, T.g0l, N, c, m, inv_rho, mmr, mu_phi, T.ph.gam3, T.ph.om_g, v, post[1],
+                                    tid, rest[1]);
   }
-  t3_sums<Q>(T, 0, x, y, z, c, in, post[0], live, tid, rest[0]);
-  __syncthreads();
-  if (fluid)
-    psi = t3_collide_ch<Q, ODD>(T, T.h, T.h0l, N, c, m, inv_rho, mmr, mu_psi, T.ph.gam3h, T.ph.om_h, u, post[0], tid,
-                                rest[2]);
-  t3_sums<Q>(T, 1, x, y, z, c, in, post[1], live, tid, rest[1]);
-  __syncthreads();
-  t3_sums<Q>(T, 2, x, y, z, c, in, post[0], live, tid, rest[2]);
+  if constexpr (SUMS) {
+    t3_sums<Q>(T, 0, x, y, z, c, in, post[0], live, tid, rest[0]);
+    __syncthreads();
+  }
+  if (STRAIGHT || fluid)
+    psi = t3_collide_ch<Q, ODD, NT>(T, T.h, T.h0l, N, c, m, inv_rho, mmr, mu_psi, T.ph.gam3h, T.ph.om_h, u, post[0],
+                                    tid, rest[2]);
+  if constexpr (SUMS) {
+    t3_sums<Q>(T, 1, x, y, z, c, in, post[1], live, tid, rest[1]);
+    __syncthreads();
+    t3_sums<Q>(T, 2, x, y, z, c, in, post[0], live, tid, rest[2]);
+  }
   if (!fluid || !bits) return;
   // moving halfway bounce-back, as bounce_back() for each population
 #pragma unroll
@@ -2403,6 +2430,18 @@ static T3View<Q> t3_view(const LaunchArgs &a) {
   return T;
 }
 
+// Whether the collide sums the next step's moments.  The sums and k3_combine save
+// a pass over the populations, but while these stay in the caches that pass is
+// cheaper than three barriers and 36 B/cell of sums (a step with the sums and
+// with the pass: 100x100 13.0 and 9.6 us, 64x64x32 28.0 and 22.2, 1024x1024 74.6
+// and 72.7; 128x96x96 150 and 156, 2048x2048 281 and 296, 256x128x128 545 and
+// 602).  With masks in 3D the collide without sums holds fewer registers (120
+// against 127) and no LDS: 128x128x96 with rollers 333 and 301, level at
+// 256x128x128.  The moments are the same additions either way.
+static bool t3_sums_moments(const LaunchArgs &a) {
+  return (long long)a.G.ex * a.G.ey * a.G.ez > (a.q == 9 || a.G.plain ? 1 << 20 : 1 << 22);
+}
+
 // the population passes over 64 x BY tiles in the XCD-aware block order
 // of the binary cell kernels (a tile's x neighbours on the same XCD, so the
 // cache lines that odd-parity streaming shares across a tile edge are
@@ -2428,25 +2467,6 @@ static void t3_couple(const LaunchArgs &a) {
 }
 
 template <int Q>
-static void t3_step(const LaunchArgs &a, int odd) {
-  t3_couple<Q>(a);
-  T3View<Q> T = t3_view<Q>(a);
-  const dim3 tiles = t3_tiles<Q>(a, T, odd);
-  for_walls(a, [&](auto walls) {
-    constexpr int W = decltype(walls)::value;
-    if (odd) k3_collide<Q, 1, W><<<tiles, cell_block(), 0, a.stream>>>(T);
-    else k3_collide<Q, 0, W><<<tiles, cell_block(), 0, a.stream>>>(T);
-    t3_tiles<Q>(a, T, odd ^ 1);
-    k3_combine<Q, W><<<tiles, cell_block(), 0, a.stream>>>(T, odd ^ 1);
-  });
-}
-
-void launch_step3(const LaunchArgs &a, int odd) {
-  if (a.q == 9) t3_step<9>(a, odd);
-  else t3_step<19>(a, odd);
-}
-
-template <int Q>
 static void t3_moments(const LaunchArgs &a, int odd) {
   T3View<Q> T = t3_view<Q>(a);
   const dim3 tiles = t3_tiles<Q>(a, T, odd);
@@ -2457,6 +2477,33 @@ static void t3_moments(const LaunchArgs &a, int odd) {
 void launch_moments3(const LaunchArgs &a, int odd) {
   if (a.q == 9) t3_moments<9>(a, odd);
   else t3_moments<19>(a, odd);
+}
+
+// M4 is valid before and after.
+template <int Q>
+static void t3_step(const LaunchArgs &a, int odd) {
+  t3_couple<Q>(a);
+  T3View<Q> T = t3_view<Q>(a);
+  const dim3 tiles = t3_tiles<Q>(a, T, odd);
+  const bool sums = t3_sums_moments(a);
+  for_walls(a, [&](auto walls) {
+    constexpr int W = decltype(walls)::value;
+    if (!sums) {
+      if (odd) k3_collide<Q, 1, W, false><<<tiles, cell_block(), 0, a.stream>>>(T);
+      else k3_collide<Q, 0, W, false><<<tiles, cell_block(), 0, a.stream>>>(T);
+      return;
+    }
+    if (odd) k3_collide<Q, 1, W, true><<<tiles, cell_block(), 0, a.stream>>>(T);
+    else k3_collide<Q, 0, W, true><<<tiles, cell_block(), 0, a.stream>>>(T);
+    t3_tiles<Q>(a, T, odd ^ 1);
+    k3_combine<Q, W><<<tiles, cell_block(), 0, a.stream>>>(T, odd ^ 1);
+  });
+  if (!sums) t3_moments<Q>(a, odd ^ 1);
+}
+
+void launch_step3(const LaunchArgs &a, int odd) {
+  if (a.q == 9) t3_step<9>(a, odd);
+  else t3_step<19>(a, odd);
 }
 
 void launch_observe3(const LaunchArgs &a, int odd) {

@@ -280,3 +280,18 @@ def test_the_batch_tuner_times_steps_as_the_batch_takes_them(rt):
     assert len(graphs(log)) == 4 * 2 * 2 * 2 and len({s for _, s in graphs(log)}) == 2
     assert marks and [rt.steps(h) for h in rt.lats] == [(0, 0), (0, 0)]
     assert rt.lib.fre_batch_step(B, 20) == 0
+
+
+@pytest.mark.parametrize("kind,shape,sums", [(0, (100, 90, 1), False), (0, (1025, 1024, 1), True),
+                                             (1, (32, 32, 31), False)])
+def test_ternary_steps_sum_moments_only_on_large_lattices(rt, kind, shape, sums):
+    p = rt.params(shape, kind, ternary=(0.2, 0.07, 0.9))
+    n, h, N = C.c_size_t(), C.c_void_p(), shape[0] * shape[1] * shape[2]
+    assert rt.lib.fre_footprint(C.byref(p), C.byref(n)) == 0
+    z = np.zeros(N)
+    assert rt.lib.fre_lattice_init3(C.byref(p), rt.buffer(n.value), n.value, rt.stream(), z.ctypes.data, z.ctypes.data,
+                                    None, None, None, C.byref(h)) == 0
+    rt.lats.append(h)
+    rt.clear()
+    assert rt.lib.fre_step(h, 1) == 0
+    assert launches(rt.log()) == ["k3_potential", "k3_collide", "k3_combine" if sums else "k3_moments"]
