@@ -260,13 +260,14 @@ __device__ __forceinline__ float sr_half(float v, uint32_t r) {
   return copysignf(t, v);
 }
 
-// a b + c rounded to half once, by the one instruction that does so.  The plain
-// expression leaves it to the compiler whether the conversion joins the
-// multiply-add (one rounding) or follows it (two), and it decides by what else
-// shares the conversion: two forms of one formula could store different halves.
+// a b + c, c a half, rounded to half once, by the one instruction that does so.
+// The plain expression leaves it to the compiler whether the conversion joins
+// the multiply-add (one rounding) or follows it (two), and it decides by what
+// else shares the conversion: two forms of one formula could store different
+// halves.
 __device__ __forceinline__ float half_fma(float a, float b, float c) {
   uint32_t r;  // the upper 16 bits are not written
-  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,1]" : "=v"(r) : "v"(a), "v"(b), "v"((_Float16)c));
   return __half2float(__builtin_bit_cast(__half, (unsigned short)r));
 }
 
@@ -283,7 +284,7 @@ template <int Q> struct Pops<Q, 0> {
   __device__ __forceinline__ float round(float v) const { return v; }
   template <bool SR>
   __device__ __forceinline__ float round_at(float v, uint32_t &) const { return v; }
-  // the value a store keeps of a b + c
+  // the value a store keeps of a b + c, c a stored value
   template <bool SR>
   __device__ __forceinline__ float fma_at(float a, float b, float c, uint32_t &) const { return __builtin_fmaf(a, b, c); }
   __device__ __forceinline__ uint32_t step_key() const { return 0u; }
@@ -316,8 +317,8 @@ template <int Q> struct Pops<Q, 1> {
       return round(v);
     }
   }
-  // the value a half store keeps of a b + c, rounded once (stochastically: the
-  // FP32 value is what is rounded)
+  // the value a half store keeps of a b + c, c a stored value, rounded once
+  // (stochastically: the FP32 value is what is rounded)
   template <bool SR>
   __device__ __forceinline__ float fma_at(float a, float b, float c, uint32_t &rs) const {
     if constexpr (SR) return round_at<SR>(__builtin_fmaf(a, b, c), rs);
