@@ -263,6 +263,7 @@ struct fre_batch {
   int parity;         // common AA parity of the members
   unsigned classes;   // bit c: class c has members
   unsigned fills;     // bit c: class c has solid cells to fill
+  unsigned solids;    // bit c: class c is stepped as lattices with solid cells all
   int rows;           // rows of 64 cells per work item
   int blocks_per_cu;  // persistent grid of the cell kernels
   int ncu;
@@ -1401,6 +1402,26 @@ void xcd_interleave(std::vector<int4> (&rows)[NXCD_HOST], std::vector<int4> &out
       if (j < q.size()) out.push_back(q[j]);
 }
 
+// The classes whose lattices are all stepped as ones with solid cells: D2Q9 FP32
+// if fills run there (batch_step_impl says why).  Its lattices between flat walls
+// are filled too then, if the list has room.
+unsigned batch_solids(const fre_batch *B) {
+  const int cls = batch_class(9, FRE_FP32);
+  size_t must = 0, flat = 0;
+  bool any = false;
+  for (const fre_lattice *L : B->slot) {
+    if (!L) continue;
+    const bool here = batch_class(L->a.q, L->a.storage) == cls;
+    if (!L->a.G.flat) {
+      must += L->fill_host.size();
+      any = any || (here && !L->fill_host.empty());
+    } else if (here) {
+      flat += L->fill_host.size();
+    }
+  }
+  return any && must + flat <= (size_t)B->cap_fill ? 1u << cls : 0u;
+}
+
 // Rebuild and upload the instance table and the work lists, grouped by
 // class; the ranges tell each class's persistent kernels what to walk.
 fre_status batch_rebuild(fre_batch *B) {
@@ -1411,6 +1432,7 @@ fre_status batch_rebuild(fre_batch *B) {
   B->h_fill.clear();
   B->h_range.assign(BATCH_RANGE * N_BATCH_CLASSES, 0);
   unsigned classes = 0, fills = 0;
+  const unsigned solids = batch_solids(B);
   for (int cls = 0; cls < N_BATCH_CLASSES; ++cls) {
     int *rg = &B->h_range[BATCH_RANGE * cls];
     rg[0] = (int)B->h_work.size();
@@ -1431,8 +1453,10 @@ fre_status batch_rebuild(fre_batch *B) {
       fre_lattice *L = B->slot[k];
       if (!L || batch_class(L->a.q, L->a.storage) != cls) continue;
       classes |= 1u << cls;
-      B->h_inst[k] = inst_of(L, B->base);
-      const Geom &G = L->a.G;
+      Inst &I = B->h_inst[k];
+      I = inst_of(L, B->base);
+      if ((solids >> cls) & 1) I.G.flat = I.G.plain = 0;
+      const Geom &G = I.G;
       const int gx = (G.ex + 63) / 64, gy = (G.ey + B->rows - 1) / B->rows;
       for (int z = 0; z < G.ez; ++z)
         for (int by = 0; by < gy; ++by) {
@@ -1467,11 +1491,13 @@ fre_status batch_rebuild(fre_batch *B) {
     HIP_TRY(hipMemcpyAsync(B->d_fill, B->h_fill.data(), B->h_fill.size() * sizeof(int2), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipMemcpyAsync(B->d_range, B->h_range.data(), BATCH_RANGE * N_BATCH_CLASSES * sizeof(int), hipMemcpyHostToDevice, B->stream));
   HIP_TRY(hipStreamSynchronize(B->stream));
-  // a class's graphs launch one sequence, with or without fills, over lists whose
+  // a class's graphs launch one sequence, with or without fills and for solid cells
+  // or any, over lists whose
   // lengths they read in device memory: they stay valid while it is absent
-  batch_reset_graph(B, fills ^ B->fills);
+  batch_reset_graph(B, (fills ^ B->fills) | (solids ^ B->solids));
   B->classes = classes;
   B->fills = fills;
+  B->solids = solids;
   return FRE_OK;
 }
 
@@ -1486,6 +1512,7 @@ BatchArgs batch_args(const fre_batch *B) {
   b.grid_cells = B->grid_cells;
   b.grid_fill = B->grid_fill;
   b.fills = B->fills;
+  b.solids = B->solids;
   b.grid_cols = 8 * B->ncu;
   b.rows = B->rows;
   b.stream = B->stream;
@@ -1667,7 +1694,7 @@ fre_status fre_batch_create(void *device_buf, size_t bytes, void *hip_stream, in
   B->d_range = (int *)(B->base + P.o_range);
   B->slot.assign(max_slots, nullptr);
   B->parity = 0;
-  B->classes = B->fills = 0;
+  B->classes = B->fills = B->solids = 0;
   int dev = 0, ncu = 256;
   if (hipGetDevice(&dev) == hipSuccess) {
     int v = 0;

@@ -142,6 +142,7 @@ struct BatchArgs {
   const int *range;
   int grid_cells, grid_fill;
   unsigned fills;  // bit c: class c has solid cells to fill
+  unsigned solids;  // bit c: all lattices of class c come as ones with solid cells (Geom::flat, plain clear)
   int grid_cols;  // potential columns: 8 blocks per CU (the LDS ring fits 10)
   int rows;  // rows of 64 cells per work item (and per block)
   hipStream_t stream;

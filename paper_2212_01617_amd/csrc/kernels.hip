@@ -1332,7 +1332,7 @@ __device__ __forceinline__ LatView<Q, S> view_of(char *base, const Inst &I) {
   return L;
 }
 
-template <int Q, int S, int STAGE, int ODD>
+template <int Q, int S, int STAGE, int ODD, int W = W_ANY>
 __global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_cells(char *base, const Inst *__restrict__ inst, const int4 *__restrict__ work,
                                                         const int *__restrict__ range) {
   const int start = range[0], n = range[1];
@@ -1343,10 +1343,10 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_batch_cells(char *base, const 
     const int y = __builtin_amdgcn_readfirstlane(it.z * (int)blockDim.y + (int)threadIdx.y);
     const bool in = x < L.G.ex && y < L.G.ey;
     if (STAGE == ST_COLLIDE) {
-      stage_collide<Q, S, ODD, W_ANY>(L, x, y, z, in);
+      stage_collide<Q, S, ODD, W>(L, x, y, z, in);
       if (ByProduct<S>::on) __syncthreads();  // the tile buffer is reused by the next item
     } else if (in) {
-      run_stage<Q, S, STAGE, ODD, W_ANY>(L, x, y, z);
+      run_stage<Q, S, STAGE, ODD, W>(L, x, y, z);
     }
   }
 }
@@ -2385,8 +2385,19 @@ static void batch_step_impl(const BatchArgs &b, int cls, int odd) {
   if (fills) k_batch_fill<Q, S, 0><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
   k_batch_potential<Q, S><<<b.grid_cols, bl, 0, b.stream>>>(b.base, b.inst, b.cols, rp);
   if (fills) k_batch_fill<Q, S, 1><<<b.grid_fill, 256, 0, b.stream>>>(b.base, b.inst, b.fill, rf);
-  if (odd) k_batch_cells<Q, S, ST_COLLIDE, 1><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
-  else k_batch_cells<Q, S, ST_COLLIDE, 0><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
+  auto collide = [&](auto walls) {
+    constexpr int W = decltype(walls)::value;
+    if (odd) k_batch_cells<Q, S, ST_COLLIDE, 1, W><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
+    else k_batch_cells<Q, S, ST_COLLIDE, 0, W><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
+  };
+  // A D2Q9 FP32 class in which fills run anyway takes the collide for solid cells,
+  // its lattices between flat walls too: four four-roller lattices of 128x128
+  // 24.0 -> 22.7 us a step, two of them beside two between walls 23.4 -> 22.3.  In
+  // FP16 that is slower (eight of 512x512 104.9 -> 110.6), in 3D it holds more
+  // registers.
+  constexpr int WS = Q == 9 && S == 0 ? W_SOLIDS : W_ANY;
+  if ((b.solids >> cls) & 1) collide(std::integral_constant<int, WS>{});
+  else collide(std::integral_constant<int, W_ANY>{});
   if (ByProduct<S>::on) {
     if (odd) k_batch_cells<Q, S, ST_COMBINE, 0><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);
     else k_batch_cells<Q, S, ST_COMBINE, 1><<<b.grid_cells, bl, 0, b.stream>>>(b.base, b.inst, b.work, rc);

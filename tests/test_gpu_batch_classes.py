@@ -100,3 +100,27 @@ def test_roller_lattice_joins_and_leaves_a_class_of_flat_walls(kind, shape, stor
     srol.step(22)
     same((flat, sflat), (rol, srol))
     B.close()
+
+
+@pytest.mark.parametrize("room", [False, True])
+def test_flat_walls_beside_rollers_with_and_without_room_for_their_fills(room):
+    """D2Q9 FP32: beside a roller lattice the member between flat walls is filled as
+    well, unless the batch's list holds the roller lattice's fills alone."""
+    shape = (70, 33, 1)
+    nx, ny, nz = shape
+    mask = np.zeros((nz, ny, nx), np.uint8)
+    mask[:, 2:5, 10:13] = 2
+    rp = F.make_params(0, shape, rollers=[((11.0, 3.0, 0.0), 0.002, 2, 2.0)], A=0.04, kappa=0.09)
+    phi0, _, _ = case_inputs(0, shape, radius=5, xi=1.5, seed=3)
+    pairs = [[_make(0, shape, 0) for _ in range(2)],
+             [F.Lattice(rp, phi0, mask=mask, stream=torch.cuda.Stream()) for _ in range(2)]]
+    needs = [F.Batch.needs(p[0]) for p in pairs]
+    B = F.Batch(2, sum(w for w, _ in needs), needs[1][1] + (needs[0][1] if room else 0))
+    for p in pairs:
+        B.add(p[0])
+    B.step(21)
+    for a, b in pairs:
+        b.step(21)
+        for x, y in zip(a.populations(), b.populations()):
+            assert np.isfinite(x).all() and np.array_equal(x, y)
+    B.close()
