@@ -164,6 +164,10 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 hipError_t hipEventSynchronize(hipEvent_t) { LOCK; MAY_FAIL("hipEventSynchronize"); return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *out) {
+  *out = s && S(s)->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   LOCK;
   MAY_FAIL("hipStreamBeginCapture");

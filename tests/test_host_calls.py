@@ -167,26 +167,34 @@ def graphs(log):
     return [tuple(line.split()[1::2]) for line in log if line.startswith("graph ")]
 
 
+TURN = 64     # runs of 16 steps that a class is given before the next one
+
+
 def test_classes_of_a_batch_are_queued_in_turn(rt):
-    """Each class gets a run of steps before any gets its next one: a queue
-    filled with one class's whole call would hold the others back."""
+    """Each class gets a bounded number of steps before the others get theirs: a
+    queue filled with one class's whole call would hold the others back."""
     B, st = rt.batch([rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8)), rt.lattice((64, 8, 8), storage=1)])
     rt.clear()
-    assert rt.lib.fre_batch_step(B, 52) == 0      # three runs of 16 and two pairs
-    order = [s for _, s in graphs(rt.log())]
-    assert len(order) == 15 and len(set(order)) == 3
-    for k in range(0, 15, 3):
-        assert set(order[k:k + 3]) == set(order[:3])
+    assert rt.lib.fre_batch_step(B, 2 * 16 * TURN + 52) == 0
+    turns = []
+    for _, s in graphs(rt.log()):
+        if not turns or turns[-1][0] != s:
+            turns.append([s, 0])
+        turns[-1][1] += 1
+    assert [n for _, n in turns] == 6 * [TURN] + 3 * [5]       # 52 steps: three runs and two pairs
+    for k in (0, 3, 6):
+        assert [s for s, _ in turns[k:k + 3]] == [s for s, _ in turns[:3]]
+    assert len({s for s, _ in turns}) == 3
 
 
-def test_a_failed_launch_between_runs_leaves_the_members_usable(rt):
+def test_a_failed_launch_between_turns_leaves_the_members_usable(rt):
     mem = [rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))]
     B, st = rt.batch(mem)
-    for nth, taken in ((1, 0), (3, 16), (2, None)):
+    for nth, taken in ((1, 0), (2 * TURN + 1, 16 * TURN), (2, None)):
         before = [rt.steps(h)[0] for h in mem]
         rt.clear()
         rt.fail("hipGraphLaunch", nth)
-        assert rt.lib.fre_batch_step(B, 48) == F.FRE_EDEVICE
+        assert rt.lib.fre_batch_step(B, 16 * TURN + 48) == F.FRE_EDEVICE
         after = [rt.steps(h) for h in mem]
         if taken is None:     # one class is a run ahead of the other
             assert all(s == 1 for _, s in after)
@@ -198,6 +206,31 @@ def test_a_failed_launch_between_runs_leaves_the_members_usable(rt):
         # what ran is joined to the batch's stream, what did not run is not
         assert (f"wait {st}" in rt.log()) == (taken > 0)
         assert rt.lib.fre_batch_step(B, 16) == 0
+
+
+def test_a_failed_launch_of_a_single_class_keeps_the_steps_taken(rt):
+    mem = [rt.lattice((70, 9, 8)), rt.lattice((40, 9, 8))]
+    B, _ = rt.batch(mem)
+    for nth, taken in ((3, 32), (5, 50)):
+        before = [rt.steps(h)[0] for h in mem]
+        rt.fail("hipGraphLaunch", nth)
+        assert rt.lib.fre_batch_step(B, 52) == F.FRE_EDEVICE
+        assert [rt.steps(h) for h in mem] == [(b + taken, 0) for b in before]
+
+
+def test_steps_on_a_capturing_stream_draw_in_no_other(rt):
+    """The caller captures the batch's stream: nothing is recorded on, or waited
+    for by, the batch's own streams, which the capture would swallow."""
+    cap = rt.stream()
+    B, st = rt.batch([rt.lattice((70, 9, 1), kind=0), rt.lattice((70, 9, 8))], stream=cap)
+    assert rt.lib.fre_batch_step(B, 18) == 0        # both classes' graphs
+    assert rt.lib.hipStreamBeginCapture(cap, 0) == 0
+    rt.clear()
+    assert rt.lib.fre_batch_step(B, 16) == F.FRE_EDEVICE
+    g = C.c_void_p()
+    assert rt.lib.hipStreamEndCapture(cap, C.byref(g)) == 0
+    assert not any(line.startswith(("wait", "record", "graph")) for line in rt.log())
+    assert [rt.steps(h) for h in rt.lats] == [(18, 0)] * 2
 
 
 @pytest.mark.parametrize("how", [dict(prio=-1), dict(mask=0xFFFF)])
