@@ -183,9 +183,11 @@ Plan make_plan(const fre_params *p) {
   // FP32: per 64-cell row segment, the post-collision (f, g) of the
   // populations that leave it through its first and last column
   P.o_XE = bp ? take((size_t)(P.ncell / 64) * 2 * (P.q == 19 ? 5 : 3) * 8) : 0;
-  // ternary: the same for three populations, a float per cell and group
-  P.o_P3 = t3 ? take((size_t)P.ncell * 4 * (P.q == 19 ? 9 : 3)) : 0;
-  P.o_XE3 = t3 ? take((size_t)(P.ncell / 64) * 2 * (P.q == 19 ? 5 : 3) * 12) : 0;
+  // ternary: the same for three populations, a float per cell and group, on the
+  // lattices whose collide may sum
+  const bool t3s = t3 && (long long)P.ext[0] * P.ext[1] * P.ext[2] > T3_SUMS_CELLS;
+  P.o_P3 = t3s ? take((size_t)P.ncell * 4 * (P.q == 19 ? 9 : 3)) : 0;
+  P.o_XE3 = t3s ? take((size_t)(P.ncell / 64) * 2 * (P.q == 19 ? 5 : 3) * 12) : 0;
   P.o_AUX = take((size_t)P.ncell * 16);
   P.o_fill = take((size_t)P.ncell * 4);
   P.o_part = take((size_t)reduce_blocks() * 8 * sizeof(double));

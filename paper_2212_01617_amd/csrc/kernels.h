@@ -54,7 +54,7 @@ struct LaunchArgs {
   void *h;
   __half *h0l;
   float2 *CM;
-  float *P3, *XE3;  // first-pass moment sums and sideways populations of the collide
+  float *P3, *XE3;  // first-pass moment sums and sideways populations of the collide (large lattices, or null)
 };
 
 template <int Q, int S> inline Pops<Q, S> make_pops(const LaunchArgs &a);
@@ -188,6 +188,9 @@ void launch_pack(const LaunchArgs &a, int nx, int ny, int N, unsigned long long 
 // outside; a step leaves M valid), one step, the observables (into AUX; C, CM current), the
 // equilibrium initialisation (M filled from host fields, AUX = u0) and the
 // populations of storage cells [c0, c0 + n) as [3q + 2][n] floats.
+// Cells beyond which the collide of a ternary lattice may sum the next step's
+// moments (and needs P3 and XE3); kernels.hip, t3_sums_moments, says why.
+constexpr long long T3_SUMS_CELLS = 1 << 20;
 void launch_moments3(const LaunchArgs &a, int odd);
 void launch_step3(const LaunchArgs &a, int odd);
 void launch_observe3(const LaunchArgs &a, int odd);

@@ -2450,7 +2450,7 @@ static T3View<Q> t3_view(const LaunchArgs &a) {
 // against 127) and no LDS: 128x128x96 with rollers 333 and 301, level at
 // 256x128x128.  The moments are the same additions either way.
 static bool t3_sums_moments(const LaunchArgs &a) {
-  return (long long)a.G.ex * a.G.ey * a.G.ez > (a.q == 9 || a.G.plain ? 1 << 20 : 1 << 22);
+  return (long long)a.G.ex * a.G.ey * a.G.ez > (a.q == 9 || a.G.plain ? T3_SUMS_CELLS : 4 * T3_SUMS_CELLS);
 }
 
 // the population passes over 64 x BY tiles in the XCD-aware block order

@@ -328,3 +328,15 @@ def test_ternary_steps_sum_moments_only_on_large_lattices(rt, kind, shape, sums)
     rt.clear()
     assert rt.lib.fre_step(h, 1) == 0
     assert launches(rt.log()) == ["k3_potential", "k3_collide", "k3_combine" if sums else "k3_moments"]
+
+
+@pytest.mark.parametrize("kind,small,large,sums", [(0, (1024, 1022, 1), (1024, 1023, 1), 12.0),
+                                                   (1, (128, 128, 62), (128, 128, 63), 36.0)])
+def test_only_ternary_lattices_that_sum_moments_hold_the_sums(rt, kind, small, large, sums):
+    """With the walls' ghost layers the small one has 2^20 cells."""
+    def bytes_per_cell(shape):
+        n = C.c_size_t()
+        assert rt.lib.fre_footprint(C.byref(rt.params(shape, kind, ternary=(0.2, 0.07, 0.9))), C.byref(n)) == 0
+        return n.value / (shape[0] * (shape[1] + 2) if kind == 0 else shape[0] * shape[1] * (shape[2] + 2))
+
+    assert sums <= bytes_per_cell(large) - bytes_per_cell(small) < sums + 2.5
