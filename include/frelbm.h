@@ -15,9 +15,16 @@
  *  - Device memory is owned by the caller.  The library only borrows the
  *    buffer given to fre_lattice_init / fre_batch_create for the handle's
  *    lifetime and never frees it.  Host buffers are the caller's.
- *  - All device work is enqueued on the caller's HIP stream (hipStream_t
- *    passed as void*; NULL = the default stream).  fre_step is asynchronous;
- *    every call that returns host data synchronises that stream first.
+ *  - All device work is ordered by the caller's HIP stream (hipStream_t
+ *    passed as void*; NULL = the default stream): it starts after what is
+ *    queued there, and what is queued there later starts after it.  It runs on
+ *    that stream itself, except for the classes of a batch (fre_batch_step).
+ *    fre_step is asynchronous; every call that returns host data synchronises
+ *    that stream first.
+ *  - Field reads pass through pinned host memory that the library allocates
+ *    and keeps for the next read of any lattice: from the first lattice on a
+ *    buffer of 128 KiB, 2 or 16 MiB by the lattice's size, at most 64 MiB kept in
+ *    all, freed with the process's last lattice.
  *  - Every call returns a fre_status; on failure fre_last_error() gives a
  *    thread-local message.  Nothing throws across the ABI.  Parameters are
  *    validated before any device work is enqueued.
@@ -137,7 +144,9 @@ typedef struct fre_lattice fre_lattice;
 typedef struct fre_batch fre_batch;
 
 /* Device bytes fre_lattice_init needs for these parameters (populations in
- * place, coupling fields, mask and scratch).  No device work. */
+ * place, coupling fields, mask and scratch; with FP32 storage also sums of the
+ * next step's moments, 25 bytes a cell of a D3Q19 lattice, 38 if it is ternary
+ * and has more than 2^20 cells).  No device work. */
 fre_status fre_footprint(const fre_params *p, size_t *device_bytes);
 
 /* Create a lattice in the caller's device buffer (>= fre_footprint bytes,
@@ -200,7 +209,9 @@ fre_status fre_step(fre_lattice *L, int64_t n);
  * of n_doubles.  u includes F/2 (eq. veloMoment); P is the bulk pressure
  * cs^2 rho + rho mu_rho + phi mu_phi - psi_b (ternary: + psi mu_psi, and the
  * ternary bulk density).  Ternary lattices also take FRE_F_PSI and
- * FRE_F_MU_PSI.  Solid cells read 0.  Syncs. */
+ * FRE_F_MU_PSI.  Solid cells read 0.  Syncs.  Reads of more than 786432
+ * doubles run up to 7 host threads beside the calling one, which copy into
+ * host_out and end before the call returns. */
 fre_status fre_read_moments(fre_lattice *L, uint32_t field_mask,
                             double *host_out, size_t n_doubles);
 
@@ -336,7 +347,7 @@ fre_status fre_batch_remove(fre_batch *B, int32_t slot);
  * Runs of four steps and more replay one graph per class, the classes side by
  * side on streams of the batch's own that wait for what is queued on the
  * batch's stream and that it waits for in turn; on a stream with a priority
- * or a CU mask all of them run on that stream.
+ * or a CU mask, or under capture, all of them run on that stream.
  * FRE_ESTATE if a member has failed.  FRE_EDEVICE if a launch fails: the steps
  * taken until then count (fre_info), and if they are not the same for every
  * class, all members are put in the failed state. */

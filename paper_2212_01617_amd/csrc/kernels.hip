@@ -436,9 +436,8 @@ __device__ __forceinline__ void fluid_mean(const float *__restrict__ X, uint32_t
 // size (three dependent loads and a launch).  Without them the 400x200 D2Q9
 // step takes 15.2 instead of 19.4 us, that of 64x32x32 cells 22 instead of 27,
 // and that of 256x128x128 374 instead of 389 (together with the collide's load
-// order).  Masks, rollers
-// and walls on other axes keep the fill kernels: their ghost cells have other
-// neighbours, up to four cells from the reader.
+// order).  Masks, rollers and walls on other axes keep the fill kernels: their
+// ghost cells have other neighbours, up to four cells from the reader.
 // The second tangential component of direction i (0 in 2D).
 template <class V> __host__ __device__ constexpr int ct1(int i) { return V::D == 3 ? V::cy(i) : 0; }
 
@@ -1177,8 +1176,8 @@ __global__ __launch_bounds__(BX *MAX_ROWS) void k_potential_zm(LatView<Q, S> L, 
 // what counts: a step takes 13.0 instead of 15.2 us at 400x200 FP32, 10.2
 // instead of 12.1 at 333x150 FP16 (and 157 instead of 194 at 2048x2048, where
 // it is the bytes).  In 3D the same fusion (a block marching in z, four planes of moments
-// and three of Pi in LDS) lost: 385-411 us instead of 290 for both kernels
-// at 256x128x128 FP32, 210-235 instead of 200 in FP16, since 68 KB of LDS
+// and three of Pi in LDS) lost: 385-411 us instead of 325 for both kernels
+// at 256x128x128 FP32, 207-235 instead of 200 in FP16, since 68 KB of LDS
 // leave two blocks per CU and each plane has three barriers.
 //
 // The arithmetic is that of potential_column and of the collide on the
@@ -1361,9 +1360,8 @@ constexpr int POT_SGPRS = 80;
 // The batch potential: z-marching columns (slot, block-x, block-y, first
 // plane) of range[2] planes each, as k_potential_zm marches them.
 template <int Q, int S>
-__global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SGPRS))) void k_batch_potential(char *base, const Inst *__restrict__ inst,
-                                                               const int4 *__restrict__ cols,
-                                                               const int *__restrict__ range) {
+__global__ __launch_bounds__(BX *MAX_ROWS) __attribute__((amdgpu_num_sgpr(POT_SGPRS))) void k_batch_potential(
+    char *base, const Inst *__restrict__ inst, const int4 *__restrict__ cols, const int *__restrict__ range) {
   __shared__ PotRing ring;
   const int start = range[0], n = range[1], tz = range[2];
   for (int w = blockIdx.x; w < n; w += gridDim.x) {
@@ -1523,8 +1521,8 @@ __global__ __launch_bounds__(256) void k_read_pops(Pops<Q, S> P, const uint32_t 
 // memory, which the caller maps: the link (56 GB/s) bounds it, so one thread
 // per double, writing 512 contiguous bytes per wave, is enough.  Doing the
 // selection and the widening here sends only what was asked for; copying C
-// and AUX whole and picking them apart on one host thread took 38 ms for rho,
-// phi and u of 256x128x128 cells, this way it is 7 ms (168 MB).
+// and AUX whole and picking them apart on one host thread took 57 ms for rho,
+// phi and u of 256x128x128 cells, this way it is 4 to 8 ms by the host (168 MB).
 __global__ __launch_bounds__(256) void k_pack(const LaunchArgs a, int nx, int ny, int N, unsigned long long codes,
                                               long long g0, int n, double *__restrict__ out) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
