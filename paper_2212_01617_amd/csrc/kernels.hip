@@ -2193,13 +2193,15 @@ static void cells_launch(const LaunchArgs &a, int odd, int tick = 0) {
     if (odd) k_cells<Q, S, STAGE, 1, W><<<grid, block, 0, a.stream>>>(L);
     else k_cells<Q, S, STAGE, 0, W><<<grid, block, 0, a.stream>>>(L);
   };
-  if constexpr (Q == 19 && STAGE == ST_COLLIDE) {
+  if constexpr (Q == 19 && (STAGE == ST_COLLIDE || STAGE == ST_PRE_COLLIDE)) {
     // With masks the collide for them alone takes 139-166 registers (3 waves per
     // SIMD), the one that reads Geom's flags 106-138.  The first is faster
     // while the chip holds all waves at once (64x64x32 between walls on every
     // axis 52.4 against 54.0 us a step, FP16 49.1 against 49.7), the second
     // beyond (four rollers in 96x96x48: 80.4 against 81.4, FP16 74.5 against
-    // 76.7; in 256x256x64: 434.6 against 441.3, 320.5 against 332.4).
+    // 76.7; in 256x256x64: 434.6 against 441.3, 320.5 against 332.4;
+    // a pre-iteration of the consistent initialisation in 96x96x48: 65.4 against
+    // 67.8, FP16 61.3 against 64.2).
     if (!a.G.plain && (long long)a.G.ex * a.G.ey * a.G.ez > 3 * 4 * 256 * 64)
       return go(std::integral_constant<int, W_ANY>{});
   }

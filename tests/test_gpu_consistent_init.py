@@ -104,3 +104,21 @@ def test_error_paths():
         L2.consistent_init(phi0, None, 2)         # batch member
     assert e.value.status == F.FRE_ESTATE
     B.close()
+
+
+@pytest.mark.parametrize("nz", [40, 52])
+def test_masked_d3q19_on_either_side_of_the_collide_rule(nz):
+    """A solid box and walls on two axes: lattices of up to 196608 cells collide by
+    the kernel for solid cells, larger ones by the one that reads the flags."""
+    shape = (66, 62, nz)
+    assert (68 * 62 * (nz + 2) > 3 * 4 * 256 * 64) == (nz == 52)
+    wu = np.zeros((3, 2, 3)); wu[2, 0, 0] = -0.01; wu[0, 1, 1] = 0.012
+    phi0, rho0, u0 = case_inputs(1, shape, radius=10, xi=2.0, u_amp=0.004, seed=7)
+    mask = np.zeros((nz, 62, 66), np.uint8)
+    mask[10:14, 20:25, 8:14] = 1
+    ref, gpu = _pair(1, shape, 20, phi0=phi0, u0=u0, mask=mask, bc=(1, 0, 1), wall_u=wu,
+                     A=5.89e-3, kappa=2.36e-2, tau_f=1.0, tau_g=1.75, M=5.26)
+    _check(f"consistent_init_masked_{nz}", ref, gpu)
+    ref.step(11)
+    gpu.step(11)
+    _check(f"consistent_init_masked_{nz}_11", ref, gpu)
